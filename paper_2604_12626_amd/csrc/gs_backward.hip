@@ -1,15 +1,14 @@
 // gs_render_backward kernels.
 //
-// B1 (per tile, 256 threads = one per pixel, each wave an independent 8 x 8
-// quadrant with no workgroup barrier): walks the tile's list back to front
-// from the last composited entry of the quadrant, 64 entries at a time,
-// recomputing each alpha with exactly the forward's FP32 expression (so every
-// skip/stop/clamp decision repeats), recovering the transmittance by
+// B1 (one wave64 per 8 x 8 quadrant of a tile): walks the tile's list back
+// to front from the last composited entry of the quadrant, 64 entries at a
+// time, recomputing each alpha with exactly the forward's FP32 expression (so
+// every skip/stop/clamp decision repeats), recovering the transmittance by
 // T_i = T_{i+1} / (1 - alpha_i), and forming the screen-space adjoint of each
-// entry (u, v, conic, opacity, colour, depth).  Entries that cannot reach a
-// wave's quadrant are dropped by the same conservative bound as the forward;
-// per remaining entry the 64 lanes are summed with DPP adds and the last
-// lane issues the global float atomics (skipped when no lane contributed).
+// entry (u, v, conic, opacity, colour, depth).  Entries that cannot reach the
+// quadrant are dropped by the same conservative bound as the forward; the
+// sums over the 64 pixels of the remaining ones are taken by the matrix cores
+// (below) and leave with FP64 atomics.
 // With the forward's segment checkpoints a list is cut into segments of
 // kSegment entries (a multiple of that for lists longer than kMaxSegments
 // segments), popped by a persistent grid, every segment's walk starting from
@@ -67,41 +66,114 @@ __device__ __forceinline__ void zero_span_grid(float *p, int64_t n) {
         q[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 }
 
-// SEG: the work is the listed (tile, segment) pairs (checkpoint mode); else
-// one whole list per workgroup, its quadrant sums through LDS (WLDS) or
-// added to HBM by each wave.  Bounded to five waves per SIMD (a few
-// registers spill): the walk is bound by latency, so one more workgroup in
-// flight per CU pays.
-template <bool SEG, bool WLDS>
-__global__ void __launch_bounds__(kTilePixels, 5) backward_tile_kernel(const BackwardTileArgs a) {
-    constexpr bool kLds = SEG || WLDS;
-    __shared__ float4 s_e0[4][64], s_e1[4][64], s_e2[4][64], s_q[4][64];
-    // 64 list positions: each quadrant wave stores its per-entry sums in its
-    // own row, and the workgroup then adds the four rows in FP64 in a fixed
-    // order and issues one set of global atomics per entry (instead of one
-    // per quadrant)
-    __shared__ float s_acc[4][kLds ? kSegment * kG2D : 1];
-    __shared__ uint32_t s_gid[kLds ? kSegment : 1];
-    __shared__ uint32_t s_top;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    float4 *e0s = s_e0[wave], *e1s = s_e1[wave], *e2s = s_e2[wave], *qs = s_q[wave];
-    // work: a (view, tile) list, or with checkpoints one segment of one (the
-    // listed pairs, popped by a persistent grid); wave w owns the 8 x 8
-    // quadrant w, one pixel per lane
-    const uint32_t n_work = a.seg_list ? a.seg_list[0] : (uint32_t)a.n_items;
-    if (kLds) {
-        for (int i = threadIdx.x; i < 4 * kSegment * kG2D; i += kTilePixels) (&s_acc[0][0])[i] = 0.0f;
-        __syncthreads();
+// The screen-space sums of one entry over the 64 pixels of a quadrant are a
+// product of two small matrices, and the matrix cores take them: with
+//   g(e, p) = dL/dalpha * G   (0 where the entry is skipped or clamped)
+//   w(e, p) = alpha * T       (0 where it is skipped)
+// every adjoint of entry e is a combination of six moments of g over the
+// pixels (1, x, y, x^2, xy, y^2 with x, y the pixel relative to the
+// quadrant's centre) and four sums of w (times dL/dred, green, blue, depth of
+// the pixel).  A batch of kBatch entries writes its g and w rows to LDS (lane
+// = pixel), reads them back transposed as the A operand (row = entry, k =
+// pixel) and multiplies them with the pixels' ten features (B operand, in
+// registers for the whole walk): 16 v_mfma_f32_16x16x4_f32 per batch, exact
+// FP32 products accumulated in FP32.  The moments are shifted to the entry's
+// own centre in FP64 once per 64-entry chunk.  (Ten sums over the lanes with
+// DPP adds took 60 of 165 VALU instructions per entry, and the products they
+// summed another 30; this takes about 33.)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kBatch = 8;                // entries per batch: rows 0..7 are their g, rows 8..15 their w
+constexpr int kGwStride = 68;            // floats per row: the b128 reads of 16 rows fall on different banks
+enum { kM0 = 0, kMx, kMy, kMxx, kMxy, kMyy, kWr, kWg, kWb, kWz, kMoments };
+static_assert(kMoments <= 16, "the features are the columns of a 16 x 16 product");
+
+// The adjoints of an entry from its moments over one quadrant: with (du, dv)
+// the entry's centre relative to the quadrant's and dL/dP = o g,
+//   u, v: o (A sx + B sy), o (B sx + C sy)   with sx = sum g dx, sy = sum g dy
+//   conic: -o/2 sum g dx^2, -o sum g dx dy, -o/2 sum g dy^2;  opacity: sum g
+// m(k): moment k of the quadrant
+template <typename M>
+__device__ __forceinline__ double moment_dx(M &&m, double du) {
+    return (double)m(kMx) - du * (double)m(kM0);
+}
+template <typename M>
+__device__ __forceinline__ double moment_dy(M &&m, double dv) {
+    return (double)m(kMy) - dv * (double)m(kM0);
+}
+template <typename M>
+__device__ __forceinline__ double moment_dxx(M &&m, double du) {
+    return (double)m(kMxx) - du * ((double)m(kMx) + moment_dx(m, du));
+}
+template <typename M>
+__device__ __forceinline__ double moment_dxy(M &&m, double du, double dv) {
+    return (double)m(kMxy) - du * (double)m(kMy) - dv * moment_dx(m, du);
+}
+template <typename M>
+__device__ __forceinline__ double moment_dyy(M &&m, double dv) {
+    return (double)m(kMyy) - dv * ((double)m(kMy) + moment_dy(m, dv));
+}
+
+// One wave per workgroup walks one 8 x 8 quadrant of a (view, tile) list, or
+// with checkpoints of one segment of one, one pixel per lane; no wave waits
+// for another.  The four quadrants of an item are neighbours in one XCD's
+// share of the workgroups, so its list is gathered through one L2.  10 KB of
+// LDS and 128 registers: four waves per SIMD.
+// The adjoints of a chunk leave with one FP64 atomic per surviving (entry,
+// adjoint), consecutive lanes on consecutive adjoints of an entry: an entry's
+// ten meet in one or two cache lines (one entry per lane took twice as long
+// as the rest of the kernel).
+// Bound by the VALU (75 % of its issue; the matrix cores 25 %, the atomics
+// about 8 % of the time).  Against a 256-thread workgroup per tile whose
+// quadrants walked in step and summed with DPP adds: 16 views of 640 x 480
+// over 1.4M Gaussians 3577 -> 1600 us, a 1280 x 720 view of 1M 341 -> 196 us,
+// a 256 x 256 view of 500k in segments 52.7 -> 34.4 us.
+__global__ void __launch_bounds__(64, 4) backward_tile_kernel(const BackwardTileArgs a) {
+    // the chunk's staged survivors (u, v, a, b) (c, o, z, r) (g, b) and their
+    // list positions inside the chunk, back to front; the batch's g and w
+    // rows; after the walk the first two and the rows hold the adjoints
+    struct Stage {
+        float4 e0[64], e1[64];
+        float gw[2 * kBatch][kGwStride];
+    };
+    __shared__ __attribute__((aligned(16))) Stage s_st;
+    __shared__ float2 s_e2[64];
+    __shared__ __attribute__((aligned(16))) uint32_t s_pos[64];
+    __shared__ float s_mom[kMoments][64];  // moments of the survivors
+    __shared__ uint32_t s_id[64];          // and their instances
+    static_assert(sizeof(Stage) >= 64 * kG2D * sizeof(double), "the adjoints of a chunk fit over the staging");
+    double *out = reinterpret_cast<double *>(&s_st);
+    float4 *e0s = s_st.e0, *e1s = s_st.e1;
+    float2 *e2s = s_e2;
+    float(*gw)[kGwStride] = s_st.gw;
+    const int lane = threadIdx.x;
+    const uint64_t gt_mask = lane == 63 ? 0ull : ~0ull << (lane + 1);
+    // operand layout of v_mfma_f32_16x16x4_f32: A row / B column = lane % 16,
+    // k = lane / 16; step 4 m + c of a batch takes pixel 16 (lane / 16) + 4 m + c.
+    // Columns 0..5 are the same for every quadrant (set once), 6..9 come
+    // from the pixels' image adjoints (set per walk), the rest stay zero.
+    const int mi = lane & 15, mk = lane >> 4;
+    const bool d_col = mi >= kWr && mi < kMoments;
+    float feat[16];
+#pragma unroll
+    for (int st = 0; st < 16; ++st) {
+        const int p = 16 * mk + st;
+        const float x = (float)(p & 7) - 3.5f, y = (float)(p >> 3) - 3.5f;
+        feat[st] = mi == kM0 ? 1.0f : mi == kMx ? x : mi == kMy ? y : mi == kMxx ? x * x : mi == kMxy ? x * y
+                 : mi == kMyy ? y * y : 0.0f;
     }
-    for (uint32_t wk = blockIdx.x; wk < n_work; wk += a.n_groups) {
+    // work: quadrant (k & 3) of the (k >> 2)-th item of queue q, for workgroup
+    // 8 k + q: a (view, tile) list, or with checkpoints a listed segment of one
+    const uint32_t n_work = a.seg_list ? a.seg_list[0] : (uint32_t)a.n_items;
+    const uint32_t xq = blockIdx.x % kOrderQueues;
+    for (uint32_t k = blockIdx.x / kOrderQueues;; k += a.n_groups / kOrderQueues) {
+    const uint32_t wk = (k >> 2) * kOrderQueues + xq;
+    const int wave = (int)(k & 3u);  // the quadrant
+    if (wk >= n_work) break;
     const uint32_t entry = a.seg_list ? a.seg_list[1 + wk] : 0u;
-    // whole lists with the work order: workgroup wk takes entry wk / 8 of
-    // queue wk mod 8 (queue q holds the lists t = q mod 8, longest first, so
-    // this maps the workgroups one to one onto the lists)
+    // whole lists with the work order: queue q holds the lists t = q mod 8,
+    // longest first
     const int64_t item = a.seg_list ? (int64_t)(entry >> 6)
-                         : a.order  ? (int64_t)a.order[(int64_t)(wk % kOrderQueues) * order_stride(a.n_items) +
-                                                       wk / kOrderQueues]
+                         : a.order  ? (int64_t)a.order[(int64_t)xq * order_stride(a.n_items) + (k >> 2)]
                                     : (int64_t)wk;
     const uint32_t s = a.seg_list ? (entry & 63u) : 0u;
     const int view = (int)(item / a.T);
@@ -172,31 +244,11 @@ __global__ void __launch_bounds__(kTilePixels, 5) backward_tile_kernel(const Bac
     const uint32_t seg_end = (last_seg || from_end) ? maxlast : seg_lo + seg_len;  // state known here
     const uint32_t own_hi = from_end ? seg_lo + seg_len : seg_end;  // entries this walk adds
     const uint32_t seg_hi = seg_end < maxlast ? seg_end : maxlast;
-    // Per-entry sums over the four quadrant waves go through LDS, 64 list
-    // positions at a time, for segments of at most 64 entries (every middle
-    // one, and a last one that short) and, when the launch has many lists,
-    // for whole lists: all waves walk the same chunks, from `top` down, and
-    // after each chunk the workgroup issues one global atomic per nonzero
-    // (entry, value).  Otherwise (a longer last segment, or a few long whole
-    // lists, where waves walking in step would wait for each other) each
-    // wave adds to HBM directly, with no barrier.  Uniform per workgroup.
-    const bool lds_sum = SEG ? (middle || L <= seg_lo + (uint32_t)kSegment) : WLDS;
-    if (!lds_sum && seg_lo >= seg_hi) continue;
-    uint32_t top = seg_hi;
-    if (lds_sum) {
-        if (SEG) {
-            top = min(seg_lo + seg_len, L);
-        } else {  // the longest walk of the four quadrants
-            if (threadIdx.x == 0) s_top = 0u;
-            __syncthreads();
-            if (lane == 0) atomicMax(&s_top, seg_hi);
-            __syncthreads();
-            top = s_top;
-        }
-    }
-    {
-    // suffix colour / depth behind the current entry over its transmittance:
-    // the background at the end of the walk, else the checkpoint at seg_end
+    if (seg_lo >= seg_hi) continue;
+    // d . S, with S the suffix colour and depth behind the current entry over
+    // its transmittance (the background at the end of the walk, else the
+    // checkpoint at seg_end) and d the pixel's adjoint of colour and depth:
+    // the walk needs S only through this product
     float Sr = a.bg0, Sg = a.bg1, Sb = a.bg2, Sd = 0.0f;
     if (seg_end < maxlast && ck_ok) {
         T = ck[0];
@@ -205,138 +257,177 @@ __global__ void __launch_bounds__(kTilePixels, 5) backward_tile_kernel(const Bac
         Sb = ck[3];
         Sd = ck[4];
     }
+    float S = dR * Sr + dG * Sg + dB * Sb + dD * Sd;
+    const float dAT = dA * Tfin;
+    const float amax = __builtin_canonicalizef(a.alpha_max);  // keeps the clamp's operand out of the loop
+    // the image adjoints as feature columns; a pixel whose adjoint is not
+    // finite would reach every entry of the product, so its column entry is
+    // zero and its share is added apart (below)
+    const bool odd_px = !(isfinite(dR) && isfinite(dG) && isfinite(dB) && isfinite(dD));
+    const uint64_t odd_any = __ballot(odd_px);
+    {
+        float *st = &gw[0][0];
+        lds_wave_sync();
+        st[lane] = odd_px ? 0.0f : dR;
+        st[kGwStride + lane] = odd_px ? 0.0f : dG;
+        st[2 * kGwStride + lane] = odd_px ? 0.0f : dB;
+        st[3 * kGwStride + lane] = odd_px ? 0.0f : dD;
+        lds_wave_sync();
+        if (d_col) {
+            const f32x4 *src = reinterpret_cast<const f32x4 *>(st + (mi - kWr) * kGwStride + 16 * mk);
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const f32x4 f = src[m];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) feat[4 * m + c] = f[c];
+            }
+        }
+        lds_wave_sync();
+    }
 
     // chunks [lo, hi) of list positions, from the back (this wave's entries
-    // end at seg_hi)
-    for (int64_t hi = (int64_t)top; hi > (int64_t)seg_lo; hi -= 64) {
-        const int64_t lo = hi - 64 > (int64_t)seg_lo ? hi - 64 : (int64_t)seg_lo;
-        const bool valid = lo + lane < min(hi, (int64_t)seg_hi);
-        bool hit = false;
-        float4 q0, q1, q2;
-        uint32_t g = 0;
-        if (valid) {
-            if (pre) {  // the one chunk of a middle segment, requested up front
-                g = g_pre;
-                q0 = p0;
-                q1 = p1;
-                q2 = p2;
-            } else {
-                g = a.vals[range.x + (uint32_t)lo + lane];
-                q0 = a.rec[3 * (size_t)g];
-                q1 = a.rec[3 * (size_t)g + 1];
-                q2 = a.rec[3 * (size_t)g + 2];
-            }
-            hit = entry_reaches_box(q0.x, q0.y, q1.x, q1.y, q1.z, q1.w, a.alpha_min, bx0, by0, bx0 + 7.0f,
-                                    by0 + 7.0f);
-        }
+    // end at seg_hi); while one is walked the next chunk's records and the
+    // list values of the one after are in flight (every load unconditional:
+    // a lane past the chunk or the list's front reads an entry of the list)
+    float4 q0 = p0, q1 = p1, q2 = p2;
+    uint32_t g = g_pre, g_next = 0u;
+    const int32_t seg_a = (int32_t)seg_lo, jl = (int32_t)L - 1;
+    auto position = [&](int32_t hi) {  // this lane's position in the chunk that ends at hi
+        return range.x + (uint32_t)min(max(hi - 64, seg_a) + lane, jl);
+    };
+    if (!pre) {
+        g = a.vals[position((int32_t)seg_hi)];
+        g_next = a.vals[position((int32_t)seg_hi - 64)];
+        q0 = a.rec[3 * (size_t)g];
+        q1 = a.rec[3 * (size_t)g + 1];
+        q2 = a.rec[3 * (size_t)g + 2];
+    }
+    // a middle segment's records, requested up front, are those of its whole
+    // chunk: positions from its first entry on
+    for (int32_t hi = (int32_t)seg_hi; hi > seg_a; hi -= 64) {
+        const int32_t lo = max(hi - 64, seg_a);
+        const uint32_t id = g;
+        const float cu = q0.x, cv = q0.y, cA = q1.x, cB = q1.y, cC = q1.z, co = q1.w;
+        const bool hit = lo + lane < hi && entry_reaches_box(cu, cv, cA, cB, cC, co, a.alpha_min, bx0, by0,
+                                                             bx0 + 7.0f, by0 + 7.0f);
         const uint64_t bal = __ballot(hit);
-        if (hit) {
-            const int pos = __popcll(bal & lt_mask);
+        const int n = __popcll(bal);
+        if (hit) {  // staged back to front
+            const int pos = __popcll(bal & gt_mask);
             const Entry e = make_entry(q0, q1, q2);
             e0s[pos] = make_float4(e.u, e.v, e.a, e.b);
             e1s[pos] = make_float4(e.c, e.o, e.z, e.r);
-            e2s[pos] = make_float4(e.g, e.bl, __uint_as_float(g), __uint_as_float((uint32_t)(lo + lane)));
-            qs[pos] = make_float4(q1.x, q1.y, q1.z, 0.0f);
+            e2s[pos] = make_float2(e.g, e.bl);
+            s_pos[pos] = (uint32_t)lane;
+            s_id[pos] = id;
         }
-        __builtin_amdgcn_wave_barrier();
-        const int n = __popcll(bal);
-        for (int q = n - 1; q >= 0; --q) {
-            const float4 e0 = e0s[q], e1 = e1s[q], e2 = e2s[q];
-            const uint32_t pos = __float_as_uint(e2.w);  // list position (< maxlast <= list length)
-            float gu = 0.f, gv = 0.f, gA = 0.f, gB = 0.f, gC = 0.f, go = 0.f, gr = 0.f, gg = 0.f, gb = 0.f, gz = 0.f;
-            bool contrib = false;
-            if (pos < last) {
-                const float dx = fx - e0.x, dy = fy - e0.y;
-                const float p2 = entry_power2(e0.z, e0.w, e1.x, dx, dy);
-                const float G = fast_exp2(p2);
-                const float oG = e1.y * G;
-                const float al = fminf(a.alpha_max, oG);
-                if (!(al < a.alpha_min)) {
-                    contrib = true;
-                    const float one_m = 1.0f - al;
-                    const float r_one_m = __builtin_amdgcn_rcpf(one_m);  // 1 ulp reciprocal (one_m >= 0.01)
-                    T = T * r_one_m;  // transmittance in front of this entry
-                    const float w = al * T;
-                    gr = dR * w;
-                    gg = dG * w;
-                    gb = dB * w;
-                    gz = dD * w;
-                    const float dal = T * (dR * (e1.w - Sr) + dG * (e2.x - Sg) + dB * (e2.y - Sb) +
-                                           dD * (e1.z - Sd)) +
-                                      dA * Tfin * r_one_m;
-                    if (!(oG > a.alpha_max)) {
-                        const float4 cq = qs[q];
-                        go = dal * G;
-                        // dL/dP with P the natural-log exponent (dG/dP = G)
-                        const float dP = dal * e1.y * G;
-                        gu = dP * (cq.x * dx + cq.y * dy);
-                        gv = dP * (cq.y * dx + cq.z * dy);
-                        gA = -0.5f * dP * dx * dx;
-                        gB = -dP * dx * dy;
-                        gC = -0.5f * dP * dy * dy;
-                    }
-                    Sr = al * e1.w + one_m * Sr;
-                    Sg = al * e2.x + one_m * Sg;
-                    Sb = al * e2.y + one_m * Sb;
-                    Sd = al * e1.z + one_m * Sd;
-                }
-            }
-            contrib = contrib && pos < own_hi;  // uniform: a walk from the end passes others' entries
-            if (__ballot(contrib) == 0ull) continue;
-            gu = wave_sum_to_last(gu);
-            gv = wave_sum_to_last(gv);
-            gA = wave_sum_to_last(gA);
-            gB = wave_sum_to_last(gB);
-            gC = wave_sum_to_last(gC);
-            go = wave_sum_to_last(go);
-            gr = wave_sum_to_last(gr);
-            gg = wave_sum_to_last(gg);
-            gb = wave_sum_to_last(gb);
-            gz = wave_sum_to_last(gz);
-            if (kLds && lds_sum) {
-                if (lane == 63) {
-                    float *acc = s_acc[wave] + (pos - (uint32_t)lo) * kG2D;
-                    s_gid[pos - (uint32_t)lo] = __float_as_uint(e2.z);
-                    acc[kGU] = gu;
-                    acc[kGV] = gv;
-                    acc[kGA] = gA;
-                    acc[kGB] = gB;
-                    acc[kGC] = gC;
-                    acc[kGO] = go;
-                    acc[kGR] = gr;
-                    acc[kGG] = gg;
-                    acc[kGBl] = gb;
-                    acc[kGZ] = gz;
-                }
-            } else if (lane == 63) {
-                double *dst = a.g2d + (size_t)__float_as_uint(e2.z) * kG2D;
-                atomicAdd(dst + kGU, (double)gu);
-                atomicAdd(dst + kGV, (double)gv);
-                atomicAdd(dst + kGA, (double)gA);
-                atomicAdd(dst + kGB, (double)gB);
-                atomicAdd(dst + kGC, (double)gC);
-                atomicAdd(dst + kGO, (double)go);
-                atomicAdd(dst + kGR, (double)gr);
-                atomicAdd(dst + kGG, (double)gg);
-                atomicAdd(dst + kGBl, (double)gb);
-                atomicAdd(dst + kGZ, (double)gz);
-            }
+        if (hi - 64 > seg_a) {
+            g = g_next;
+            q0 = a.rec[3 * (size_t)g];
+            q1 = a.rec[3 * (size_t)g + 1];
+            q2 = a.rec[3 * (size_t)g + 2];
+            g_next = a.vals[position(hi - 128)];
         }
-        __builtin_amdgcn_wave_barrier();
-        if (kLds && lds_sum) {
-            // every quadrant has added its sums for this chunk: one global
-            // atomic per nonzero (entry, value), and the accumulator is cleared
-            __syncthreads();
-            for (int i = threadIdx.x; i < kSegment * kG2D; i += kTilePixels) {
-                const double v = (((double)s_acc[0][i] + (double)s_acc[1][i]) + (double)s_acc[2][i]) + (double)s_acc[3][i];
-                if (v != 0.0) atomicAdd(a.g2d + (size_t)s_gid[i / kG2D] * kG2D + (i % kG2D), v);
+        // pad to a multiple of 4 with entries of no position (never taken)
+        if (lane < ((4 - (n & 3)) & 3)) {
+            e0s[n + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            e1s[n + lane] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            e2s[n + lane] = make_float2(0.0f, 0.0f);
+            s_pos[n + lane] = ~0u;
+        }
+        lds_wave_sync();
+        const uint32_t last_in = last > (uint32_t)lo ? last - (uint32_t)lo : 0u;  // positions below it contribute
+        for (int q = 0; q < n; q += kBatch) {
+            const int nb = min(n - q, kBatch);  // entries of this batch
+            // four entries per step: their LDS reads and alphas together,
+            // then the chain through T and S
+            for (int e = 0; e < nb; e += 4) {
+                const uint4 p4 = *reinterpret_cast<const uint4 *>(&s_pos[q + e]);
+                const uint32_t pos[4] = {p4.x, p4.y, p4.z, p4.w};
+                float G[4], oG[4], at[4], r[4], c[4];
+                bool take[4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) s_acc[q][i] = 0.0f;
+                for (int u = 0; u < 4; ++u) {
+                    const float4 e0 = e0s[q + e + u], e1 = e1s[q + e + u];
+                    const float2 e2 = e2s[q + e + u];
+                    const float dx = fx - e0.x, dy = fy - e0.y;
+                    G[u] = fast_exp2(entry_power2(e0.z, e0.w, e1.x, dx, dy));
+                    oG[u] = e1.y * G[u];
+                    const float al = fminf(amax, oG[u]);
+                    take[u] = pos[u] < last_in && !(al < a.alpha_min);
+                    at[u] = take[u] ? al : 0.0f;
+                    r[u] = __builtin_amdgcn_rcpf(1.0f - at[u]);  // 1 ulp reciprocal (1 where skipped)
+                    c[u] = fmaf(dR, e1.w, fmaf(dG, e2.x, fmaf(dB, e2.y, dD * e1.z)));
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    T = T * r[u];  // transmittance in front of this entry
+                    // d . (c - S): what the entry's colour and depth change
+                    const float dc = take[u] ? c[u] - S : 0.0f;
+                    const float dal = fmaf(T, dc, dAT * r[u]);
+                    S = fmaf(at[u], dc, S);
+                    gw[e + u][lane] = take[u] && !(oG[u] > a.alpha_max) ? dal * G[u] : 0.0f;
+                    gw[kBatch + e + u][lane] = at[u] * T;
+                }
             }
-            __syncthreads();
+            lds_wave_sync();
+            // rows 4 mk + r, column mi: moments of entry (row mod kBatch),
+            // the first kBatch rows' g columns and the others' w columns
+            const int e4 = (4 * mk) % kBatch;
+            f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+            {
+                const f32x4 *row = reinterpret_cast<const f32x4 *>(&gw[mi][16 * mk]);
+                const f32x4 av[4] = {row[0], row[1], row[2], row[3]};
+#pragma unroll
+                for (int st = 0; st < 16; ++st)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[st >> 2][st & 3], feat[st], acc, 0, 0, 0);
+            }
+            const bool mine = mk < 2 ? mi < kWr : d_col;
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (mine && e4 + r < nb) s_mom[mi][q + e4 + r] = acc[r];
+            if (odd_any) {  // uniform; rare
+                lds_wave_sync();
+                const float dv[4] = {dR, dG, dB, dD};
+                for (int e = 0; e < nb; ++e) {
+                    const float w = gw[kBatch + e][lane];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const float sum = wave_sum_to_last(odd_px && w != 0.0f ? w * dv[k] : 0.0f);
+                        if (lane == 63) s_mom[kWr + k][q + e] += sum;
+                    }
+                }
+            }
+            lds_wave_sync();
         }
+        // the survivors' adjoints from their moments, each by the lane that
+        // holds its record (a walk from the list's end passes others' entries)
+        if (hit && (uint32_t)(lo + lane) < own_hi) {
+            const int pos = __popcll(bal & gt_mask);
+            auto m = [&](int j) { return s_mom[j][pos]; };
+            const double du = (double)cu - (double)(qx0 + 4), dv = (double)cv - (double)(qy0 + 4);
+            const double sx = moment_dx(m, du), sy = moment_dy(m, dv);
+            double *o = out + pos * kG2D;
+            o[kGU] = (double)co * ((double)cA * sx + (double)cB * sy);
+            o[kGV] = (double)co * ((double)cB * sx + (double)cC * sy);
+            o[kGA] = -0.5 * (double)co * moment_dxx(m, du);
+            o[kGB] = -(double)co * moment_dxy(m, du, dv);
+            o[kGC] = -0.5 * (double)co * moment_dyy(m, dv);
+            o[kGO] = (double)m(kM0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o[kGR + j] = (double)m(kWr + j);
+        } else if (hit) {
+            double *o = out + __popcll(bal & gt_mask) * kG2D;
+#pragma unroll
+            for (int j = 0; j < kG2D; ++j) o[j] = 0.0;
+        }
+        lds_wave_sync();
+        for (int i = lane; i < n * kG2D; i += 64) {
+            const double v = out[i];
+            if (v != 0.0) atomicAdd(a.g2d + (size_t)s_id[i / kG2D] * kG2D + (i % kG2D), v);
+        }
+        lds_wave_sync();
     }
-    }  // this wave's walk
     }  // work loop
     // the dense gradient planes, cleared by each workgroup once its walks
     // are done (their stores drain while later workgroups still walk)
@@ -390,16 +481,15 @@ __global__ void __launch_bounds__(1024) segment_list_kernel(const uint2 *ranges,
     build_segment_list<1024>(ranges, n_items, list, cap);
 }
 
+// waves of the segment walk's persistent grid: what the CUs hold at once (12, 16
+// and 24 per CU measured within 8 % on 1300 segments)
+constexpr int kSegWavesPerCu = 16;
 hipError_t launch_backward_tiles(BackwardTileArgs a, int n_cu, hipStream_t s) {
     if (a.n_items == 0) return hipSuccess;
-    if (!a.seg_list) {  // one workgroup per list
-        a.n_groups = (uint32_t)a.n_items;
-        // many lists (more than the GPU holds at once): fewer global atomics
-        // pay for the waves of a tile walking in step; few long lists: not
-        if (a.n_items >= 2048)
-            return launch_kernel(backward_tile_kernel<false, true>, dim3((unsigned)a.n_items), dim3(kTilePixels), s,
-                                 a);
-        return launch_kernel(backward_tile_kernel<false, false>, dim3((unsigned)a.n_items), dim3(kTilePixels), s, a);
+    if (!a.seg_list) {  // one workgroup per quadrant of a list
+        const int64_t groups = 4 * kOrderQueues * order_stride(a.n_items);
+        a.n_groups = (uint32_t)(groups < (1ll << 30) ? groups : (1ll << 30));
+        return launch_kernel(backward_tile_kernel, dim3(a.n_groups), dim3(64), s, a);
     }
     // the work list: built by the accumulator clear for up to kListInClear
     // lists, else here
@@ -408,8 +498,8 @@ hipError_t launch_backward_tiles(BackwardTileArgs a, int n_cu, hipStream_t s) {
                                            a.seg_list, (uint64_t)(a.ckpt_slots * kListPerSlot));
         if (e != hipSuccess) return e;
     }
-    a.n_groups = (uint32_t)(6 * n_cu);  // persistent: about what the CUs hold at once
-    return launch_kernel(backward_tile_kernel<true, true>, dim3(a.n_groups), dim3(kTilePixels), s, a);
+    a.n_groups = (uint32_t)(kSegWavesPerCu * n_cu);  // persistent
+    return launch_kernel(backward_tile_kernel, dim3(a.n_groups), dim3(64), s, a);
 }
 
 // ---------------------------------------------------------------------------

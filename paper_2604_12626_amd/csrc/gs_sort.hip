@@ -1164,12 +1164,6 @@ static hipError_t launch_tilescan(const uint32_t *tile_count, const uint32_t *ti
 #undef GS_TILESCAN
 }
 
-__device__ __forceinline__ void lds_wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Ascending sorting network (bitonic) over N registers, all indices fixed at
 // compile time.
 template <int N>

@@ -345,3 +345,47 @@ def test_segmented_backward_with_a_short_checkpoint_buffer(dev, orc):
     for k in SQ_FIELDS:
         err = float((d_short[k] - d_whole[k]).abs().max() / d_whole[k].abs().max())
         assert err <= 1e-4, (k, err)
+
+
+@pytest.mark.parametrize("checkpoints", [False, True], ids=["whole_lists", "segmented"])
+def test_backward_nonfinite_pixel_adjoint_stays_with_its_gaussians(dev, checkpoints):
+    """An infinite and a NaN image adjoint at two pixels reach the Gaussians
+    those pixels composited and no others: every other Gaussian's gradient is
+    the one with the two adjoints at zero (the sums over a quadrant are a
+    matrix product, where a non-finite column would reach every entry).  The
+    two runs differ by the order of FP64 atomics and by which pixels add zero,
+    so 1e-6 of a block's largest gradient bounds the difference."""
+    import torch
+    from paper_2604_12626_amd import render
+    W, H = 75, 53  # partial tiles on both axes
+    g = synth.gaussians_cube(3000, np.random.default_rng(91), sh_degree=1)
+    cams = torch.from_numpy(synth.identity_camera(96.0, 96.0, W / 2, H / 2)[None]).to(dev)
+    tg = to_dev(g, dev)
+    r = render.Renderer(W, H, capacity=1 << 18, device=dev, checkpoints=checkpoints)
+    f = r.render([tg], cams, [[0]])
+    G = [torch.from_numpy(x).to(dev) for x in _random_adjoints(np.random.default_rng(92), 1, H, W)]
+    px = [(20, 30, float("inf")), (44, 61, float("nan"))]
+    for y, x, _ in px:
+        G[0][0, y, x, 1] = 0.0
+    want = _np(r.backward([tg], cams, [[0]], f, *G)[0])
+    for y, x, v in px:
+        G[0][0, y, x, 1] = v
+    got = _np(r.backward([tg], cams, [[0]], f, *G)[0])
+    n = len(g["means"])
+    reached, unsure = np.zeros(n, bool), np.zeros(n, bool)
+    for y, x, _ in px:
+        a, b = f.ranges[(y // 16) * r.TX + x // 16].tolist()
+        ids = f.vals[a:b].cpu().numpy()
+        q = f.rec[f.vals[a:b].long()].cpu().numpy().astype(np.float64)
+        dx, dy = x + 0.5 - q[:, 0], y + 0.5 - q[:, 1]
+        al = q[:, 7] * np.exp(-0.5 * (q[:, 4] * dx * dx + q[:, 6] * dy * dy) - q[:, 5] * dx * dy)
+        in_walk = np.arange(b - a) < int(f.n_contrib[0, y, x])
+        reached[ids[in_walk & (al > 1.001 / 255)]] = True
+        unsure[ids[in_walk & (np.abs(al * 255 - 1) <= 1e-3)]] = True
+    assert reached.sum() >= 4
+    assert not np.isfinite(got["sh"][reached]).all(axis=(1, 2)).any()
+    rest = ~reached & ~unsure
+    for k in SQ_FIELDS:
+        err = np.abs(got[k][rest] - want[k][rest]).max() / np.abs(want[k]).max()
+        say("  %s: %.2e of the block's largest" % (k, err))
+        assert err <= 1e-6

@@ -914,15 +914,15 @@ hipError_t launch_tile_order(const uint32_t *ranges, int64_t n_items, uint32_t *
 }
 
 // Tile sorts by bucket length (class: list part and kernel): up to
-// kTinySortCap entries one wave (class 4, eight entries per thread), up to
-// kSmallSortCap a 256-thread workgroup (class 3, eight each), up to
-// kMidSortCap a 256-thread workgroup (class 2, sixteen each, four resident
-// per CU), up to kLargeSortCap a 512-thread workgroup (class 1, sixteen
-// each, two per CU), longer ones a 1024-thread workgroup (class 0, sixteen
-// each: kTileSortCap in LDS, beyond that runs and merges).
+// kTinySortCap entries one wave (class 4), up to kSmallSortCap 256 threads
+// (class 3), up to kMidSortCap 512 threads (class 2), up to kLargeSortCap a
+// 1024-thread workgroup (class 1), eight entries per thread; longer ones a
+// 1024-thread workgroup with sixteen each (class 0: kTileSortCap in LDS,
+// beyond that runs and merges).
 constexpr int kTinySortCap = 512;
-constexpr int kSmallSortBlock = 256, kSmallSortCap = 2048, kMidSortCap = 4096;
-constexpr int kLargeSortBlock = 512, kLargeSortCap = 8192;
+constexpr int kSmallSortBlock = 256, kSmallSortCap = 2048;
+constexpr int kMidSortBlock = 512, kMidSortCap = 4096;
+constexpr int kLargeSortBlock = 1024, kLargeSortCap = 8192;
 constexpr int kTileSortBlock = 1024, kTileSortCap = 16384;
 constexpr int kSortClasses = 5;
 
@@ -1281,6 +1281,205 @@ __device__ __forceinline__ void merge_sort_lds(uint64_t *s, const uint64_t *in, 
     }
 }
 
+// Spread sort of the L entries at in[0, L) (1 <= L <= NT * ITEMS, entries
+// distinct): every entry is placed near its final position by its depth
+// alone, then ranked among the few that share its bucket.  A coarse histogram
+// over COARSE equal steps of the depth bits gives the distribution of the
+// tile's depths (a wall fills a few steps, most are empty); inside its step an
+// entry's bucket is interpolated over as many buckets as the step has
+// entries (2^SHIFT entries a bucket), so that the buckets hold about one
+// entry each whatever the distribution: an entry meets 1.8 to 1.9 entries
+// (itself among them) in its bucket on rooms and avatars, at most 10.  Depths
+// that do not spread (many equal ones) are told by a bucket of more than
+// kSpreadMost entries: then nothing is written, false is returned, and the
+// caller merge sorts.  A dozen LDS operations per entry and ten barriers,
+// where the merge sort takes a binary search and a dependent merge per level.
+// Output as for merge_sort_lds.
+constexpr uint32_t kSpreadMost = 64;
+
+template <int NT, int ITEMS>
+struct SpreadLds {
+    static constexpr int CAP = NT * ITEMS;
+    static constexpr int SHIFT = CAP > 8192 ? 1 : 0;     // so that the largest fits the LDS
+    static constexpr int COARSE = NT == 64 ? 64 : 256;
+    static constexpr int WORDS = (CAP >> SHIFT) / 2;     // two 16-bit bucket counters per word
+    union {
+        uint64_t s[CAP];                  // the entries
+        uint64_t merge[CAP + CAP / 8];    // or the merge sort's rows
+        struct {
+            uint64_t pad[CAP];
+            uint32_t cnt[WORDS + 1];      // bucket counts, then bucket starts (one past the end too)
+            uint32_t coarse[COARSE + 1];  // entries per step, then first entry of every step
+            uint32_t lo[NT / 64], hi[NT / 64], sum[NT / 64], crowded;
+        } b;
+    };
+};
+
+template <int NT, int ITEMS, bool ONE_WAVE>
+__device__ __forceinline__ bool spread_sort_lds(SpreadLds<NT, ITEMS> &M, const uint64_t *in, uint32_t L, uint64_t thi,
+                                                uint64_t *keys, uint32_t *vals, uint64_t *raw, uint32_t tid) {
+    using Lds = SpreadLds<NT, ITEMS>;
+    constexpr int SHIFT = Lds::SHIFT, COARSE = Lds::COARSE;
+    auto sync = [] {
+        if (ONE_WAVE) lds_wave_sync();
+        else __syncthreads();
+    };
+    const uint32_t lane = tid & 63u, wave = tid >> 6;
+    uint64_t x[ITEMS];
+#pragma unroll
+    for (int m = 0; m < ITEMS; ++m)  // loads in flight together, clamped in bounds
+        if ((uint32_t)m * NT < L) x[m] = in[min((uint32_t)m * NT + tid, L - 1u)];
+    const uint32_t n_buckets = ((L - 1u) >> SHIFT) + 1u, n_words = (n_buckets + 1u) >> 1;
+    for (uint32_t k = tid; k < n_words; k += NT) M.b.cnt[k] = 0u;
+    for (uint32_t k = tid; k < COARSE; k += NT) M.b.coarse[k] = 0u;
+    if (tid == 0) M.b.crowded = 0u;
+    // least and greatest depth bits of the tile
+    uint32_t lo = ~0u, hi = 0u;
+#pragma unroll
+    for (int m = 0; m < ITEMS; ++m)
+        if ((uint32_t)m * NT < L) {
+            lo = min(lo, (uint32_t)(x[m] >> 32));
+            hi = max(hi, (uint32_t)(x[m] >> 32));
+        }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, off, 64));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, off, 64));
+    }
+    if (!ONE_WAVE && lane == 0) {
+        M.b.lo[wave] = lo;
+        M.b.hi[wave] = hi;
+    }
+    sync();
+    if (!ONE_WAVE)
+#pragma unroll
+        for (int k = 0; k < NT / 64; ++k) {
+            lo = min(lo, M.b.lo[k]);
+            hi = max(hi, M.b.hi[k]);
+        }
+    // step and place inside it (16 bits each) of every entry; float rounding
+    // keeps the order of the depths
+    const float scale = (float)(COARSE * 65536) / ((float)(hi - lo) + 1.0f);
+    uint32_t u[ITEMS];
+#pragma unroll
+    for (int m = 0; m < ITEMS; ++m)
+        if ((uint32_t)m * NT < L) {
+            u[m] = min((uint32_t)((float)((uint32_t)(x[m] >> 32) - lo) * scale), (uint32_t)(COARSE * 65536 - 1));
+            if ((uint32_t)m * NT + tid < L) atomicAdd(&M.b.coarse[u[m] >> 16], 1u);
+        }
+    sync();
+    if (tid < 64) {  // first entry of every step
+        constexpr int PER = COARSE / 64;
+        uint32_t c[PER], own = 0u;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            c[k] = M.b.coarse[lane * PER + k];
+            own += c[k];
+        }
+        uint32_t incl = own;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = __shfl_up(incl, off, 64);
+            if (lane >= (uint32_t)off) incl += y;
+        }
+        uint32_t run = incl - own;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            M.b.coarse[lane * PER + k] = run;
+            run += c[k];
+        }
+        if (lane == 63) M.b.coarse[COARSE] = run;
+    }
+    sync();
+    // bucket and arrival in it
+#pragma unroll
+    for (int m = 0; m < ITEMS; ++m)
+        if ((uint32_t)m * NT + tid < L) {
+            const uint32_t c = u[m] >> 16, first = M.b.coarse[c], n = M.b.coarse[c + 1] - first;
+            const uint32_t b = (first + (((u[m] & 0xFFFFu) * n) >> 16)) >> SHIFT, sh = (b & 1u) << 4;
+            const uint32_t old = atomicAdd(&M.b.cnt[b >> 1], 1u << sh);
+            u[m] = b | (((old >> sh) & 0xFFFFu) << 16);
+        }
+    sync();
+    {  // bucket starts: consecutive words per thread
+        constexpr int PER = (Lds::WORDS + NT - 1) / NT;
+        uint32_t w[PER], own = 0u;
+        bool crowd = false;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const uint32_t i = tid * PER + k;
+            w[k] = i < n_words ? M.b.cnt[i] : 0u;
+            own += (w[k] & 0xFFFFu) + (w[k] >> 16);
+            crowd = crowd || (w[k] & 0xFFFFu) > kSpreadMost || (w[k] >> 16) > kSpreadMost;
+        }
+        uint32_t incl = own;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = __shfl_up(incl, off, 64);
+            if (lane >= (uint32_t)off) incl += y;
+        }
+        uint32_t run = incl - own;
+        if (!ONE_WAVE) {
+            if (lane == 63) M.b.sum[wave] = incl;
+            sync();
+            for (uint32_t k = 0; k < wave; ++k) run += M.b.sum[k];
+        }
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const uint32_t i = tid * PER + k, mid = run + (w[k] & 0xFFFFu);
+            if (i < n_words) M.b.cnt[i] = run | (mid << 16);
+            run = mid + (w[k] >> 16);
+        }
+        if (tid == 0) M.b.cnt[n_words] = L;  // one past the last bucket, where it is not an upper half
+        if (crowd) M.b.crowded = 1u;
+    }
+    sync();
+    if (M.b.crowded) return false;  // uniform
+    auto start = [&](uint32_t b) { return (M.b.cnt[b >> 1] >> ((b & 1u) << 4)) & 0xFFFFu; };
+#pragma unroll
+    for (int m = 0; m < ITEMS; ++m)
+        if ((uint32_t)m * NT + tid < L) M.s[start(u[m] & 0xFFFFu) + (u[m] >> 16)] = x[m];
+    sync();
+    // rank inside the bucket
+#pragma unroll
+    for (int m = 0; m < ITEMS; ++m)
+        if ((uint32_t)m * NT + tid < L) {
+            const uint32_t b = u[m] & 0xFFFFu, b0 = start(b), b1 = start(b + 1u);
+            uint32_t r = b0;
+            for (uint32_t j = b0; j < b1; ++j) r += M.s[j] < x[m] ? 1u : 0u;
+            u[m] = r;
+        }
+    sync();
+#pragma unroll
+    for (int m = 0; m < ITEMS; ++m)
+        if ((uint32_t)m * NT + tid < L) M.s[u[m]] = x[m];
+    sync();
+#pragma unroll
+    for (int m = 0; m < ITEMS; ++m) {
+        const uint32_t i = (uint32_t)m * NT + tid;
+        if (i < L) {
+            const uint64_t y = M.s[i];
+            if (raw) {
+                raw[i] = y;
+            } else {
+                keys[i] = thi | (y >> 32);
+                vals[i] = (uint32_t)y;
+            }
+        }
+    }
+    return true;
+}
+
+// the spread sort, or where the depths do not spread the merge sort
+template <int NT, int ITEMS, bool ONE_WAVE>
+__device__ __forceinline__ void sort_lds(SpreadLds<NT, ITEMS> &M, const uint64_t *in, uint32_t L, uint64_t thi,
+                                         uint64_t *keys, uint32_t *vals, uint64_t *raw, uint32_t tid) {
+    if (spread_sort_lds<NT, ITEMS, ONE_WAVE>(M, in, L, thi, keys, vals, raw, tid)) return;
+    if (ONE_WAVE) lds_wave_sync();
+    else __syncthreads();  // the counters are read; their LDS is the merge sort's
+    merge_sort_lds<NT, ITEMS, ONE_WAVE>(M.merge, in, L, thi, keys, vals, raw, tid);
+}
+
 // dst[i] = f(src[i]) for i < cnt by NT threads, eight loads in flight per
 // thread (clamped in bounds) before their stores
 template <int NT, typename F>
@@ -1398,11 +1597,13 @@ __device__ __forceinline__ void merge_tile_runs(uint64_t *bucket, uint64_t *keys
 // (instance) written to the tile's range.  Besides the five classes, two
 // groupings for launches of few tiles, where one launch for several classes
 // keeps every tile in flight at once: kSortShort (classes 3 and 4, up to 2048
-// entries, 256 threads: their 18 KB of LDS let eight workgroups share a CU,
-// so 2048 tiles sort in one round) and kSortLong (classes 0..2, 1024 threads,
-// a tile longer than CAP sorted as runs and merged by its own workgroup).  With sixteen
-// entries per thread, a bucket that fits eight per thread takes eight (more
-// threads at work).
+// entries, 256 threads: their 21 KB of LDS let seven workgroups share a CU,
+// so 1792 tiles sort in one round) and kSortLong (classes 0..2, 1024 threads,
+// a tile longer than CAP sorted as runs and merged by its own workgroup).
+// Bound by latency: a chain of LDS round trips and barriers per tile.  The
+// spread sort against merging levels: 1200 tiles of 300 entries 13.9 -> 11.6
+// us; 18.3M entries in 19200 tiles, all classes, 357 -> 237 us; 23.0M in
+// 16384 tiles 479 -> 275 us.
 constexpr int kSortShort = 5, kSortLong = 6;
 
 template <int THREADS, int CAP, int CLASS>
@@ -1410,7 +1611,8 @@ __global__ void __launch_bounds__(THREADS) tile_sort_kernel(uint64_t *bucket, co
                                                             const uint32_t *sort_list, const uint32_t *sort_ctl,
                                                             const uint2 *run_list, uint64_t *keys, uint32_t *vals,
                                                             const int32_t *d_overflow) {
-    __shared__ uint64_t s[CAP + CAP / 8];
+    constexpr int IT = CAP / THREADS;
+    __shared__ SpreadLds<THREADS, IT> M;
     __shared__ uint32_t s_take;
     if (*d_overflow) return;
     // class 0: first the runs of the tiles longer than CAP (sorted here, raw,
@@ -1433,30 +1635,25 @@ __global__ void __launch_bounds__(THREADS) tile_sort_kernel(uint64_t *bucket, co
         if (!SMALL && idx < n_runs) {
             const uint2 tr = run_list[idx];
             const uint32_t b = ranges[2 * tr.x], L = ranges[2 * tr.x + 1] - b, off = tr.y * (uint32_t)CAP;
-            merge_sort_lds<THREADS, CAP / THREADS, false>(s, bucket + b + off, min((uint32_t)CAP, L - off), 0ull,
-                                                          nullptr, nullptr,
-                                                          (runs_in_bucket<CAP>(L) ? bucket : keys) + b + off,
-                                                          threadIdx.x);
+            sort_lds<THREADS, IT, false>(M, bucket + b + off, min((uint32_t)CAP, L - off), 0ull, nullptr, nullptr,
+                                         (runs_in_bucket<CAP>(L) ? bucket : keys) + b + off, threadIdx.x);
         } else {
             const uint32_t tile = sort_list[first + n_huge + (idx - n_runs)];
             const uint32_t b = ranges[2 * tile], L = ranges[2 * tile + 1] - b;
-            constexpr int IT = CAP / THREADS;
             if (CLASS == kSortLong && L > (uint32_t)CAP) {
                 for (uint32_t off = 0; off < L; off += (uint32_t)CAP) {
-                    merge_sort_lds<THREADS, IT, false>(s, bucket + b + off, min((uint32_t)CAP, L - off), 0ull, nullptr,
-                                                       nullptr, (runs_in_bucket<CAP>(L) ? bucket : keys) + b + off,
-                                                       threadIdx.x);
-                    __syncthreads();  // s is reused by the next run
+                    sort_lds<THREADS, IT, false>(M, bucket + b + off, min((uint32_t)CAP, L - off), 0ull, nullptr,
+                                                 nullptr, (runs_in_bucket<CAP>(L) ? bucket : keys) + b + off,
+                                                 threadIdx.x);
+                    __syncthreads();  // M is reused by the next run
                 }
-                merge_tile_runs<THREADS, CAP>(bucket, keys, vals, tile, b, L, s, &s_take);
-            } else if (IT == 16 && L <= (uint32_t)(THREADS * 8))
-                merge_sort_lds<THREADS, (IT == 16 ? 8 : IT), false>(s, bucket + b, L, (uint64_t)tile << 32, keys + b,
-                                                                    vals + b, nullptr, threadIdx.x);
-            else
-                merge_sort_lds<THREADS, IT, false>(s, bucket + b, L, (uint64_t)tile << 32, keys + b, vals + b, nullptr,
-                                                   threadIdx.x);
+                merge_tile_runs<THREADS, CAP>(bucket, keys, vals, tile, b, L, M.s, &s_take);
+            } else {
+                sort_lds<THREADS, IT, false>(M, bucket + b, L, (uint64_t)tile << 32, keys + b, vals + b, nullptr,
+                                             threadIdx.x);
+            }
         }
-        __syncthreads();  // s is reused by the next item
+        __syncthreads();  // M is reused by the next item
     }
 }
 
@@ -1486,8 +1683,7 @@ __global__ void __launch_bounds__(256) tile_sort_wave_kernel(uint64_t *bucket, c
                                                              const uint32_t *sort_list, const uint32_t *sort_ctl,
                                                              uint64_t *keys, uint32_t *vals,
                                                              const int32_t *d_overflow) {
-    constexpr int SLOTS = kTinySortCap + kTinySortCap / 8;
-    __shared__ uint64_t s[4][SLOTS];
+    __shared__ SpreadLds<64, kTinySortCap / 64> M[4];
     if (*d_overflow) return;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     uint32_t first = 0u;
@@ -1496,9 +1692,9 @@ __global__ void __launch_bounds__(256) tile_sort_wave_kernel(uint64_t *bucket, c
     for (uint32_t idx = blockIdx.x * 4u + (uint32_t)wave; idx < n_mine; idx += gridDim.x * 4u) {  // uniform per wave
         const uint32_t tile = sort_list[first + idx];
         const uint32_t b = ranges[2 * tile], L = ranges[2 * tile + 1] - b;
-        merge_sort_lds<64, kTinySortCap / 64, true>(s[wave], bucket + b, L, (uint64_t)tile << 32, keys + b, vals + b,
-                                                    nullptr, (uint32_t)lane);
-        lds_wave_sync();  // s is reused by the next tile
+        sort_lds<64, kTinySortCap / 64, true>(M[wave], bucket + b, L, (uint64_t)tile << 32, keys + b, vals + b,
+                                              nullptr, (uint32_t)lane);
+        lds_wave_sync();  // M is reused by the next tile
     }
 }
 
@@ -1675,7 +1871,7 @@ static hipError_t run_bucket_sort(const SortPlan &P, const uint32_t *tt, const f
     };
     const int64_t nt = P.n_tiles_total;
     if (!P.windowed) {
-        if ((e = launch_kernel(tile_sort_kernel<kSmallSortBlock, kSmallSortCap, kSortShort>, dim3(grid(8, nt)),
+        if ((e = launch_kernel(tile_sort_kernel<kSmallSortBlock, kSmallSortCap, kSortShort>, dim3(grid(7, nt)),
                                dim3(kSmallSortBlock), s, A.bucket, rg, cl, cc, rl, keys, vals, ov)) != hipSuccess)
             return e;
         return launch_kernel(tile_sort_kernel<kTileSortBlock, kTileSortCap, kSortLong>, dim3(grid(1, nt)),
@@ -1685,13 +1881,13 @@ static hipError_t run_bucket_sort(const SortPlan &P, const uint32_t *tt, const f
         if ((e = launch_kernel(tile_sort_wave_kernel, dim3(grid(8, (nt + 3) / 4)), dim3(256), s, A.bucket, rg, cl, cc,
                                keys, vals, ov)) != hipSuccess)
             return e;
-        if ((e = launch_kernel(tile_sort_kernel<kSmallSortBlock, kSmallSortCap, 3>, dim3(grid(8, nt)),
+        if ((e = launch_kernel(tile_sort_kernel<kSmallSortBlock, kSmallSortCap, 3>, dim3(grid(7, nt)),
                                dim3(kSmallSortBlock), s, A.bucket, rg, cl, cc, rl, keys, vals, ov)) != hipSuccess)
             return e;
-        if ((e = launch_kernel(tile_sort_kernel<kSmallSortBlock, kMidSortCap, 2>, dim3(grid(4, nt)),
-                               dim3(kSmallSortBlock), s, A.bucket, rg, cl, cc, rl, keys, vals, ov)) != hipSuccess)
+        if ((e = launch_kernel(tile_sort_kernel<kMidSortBlock, kMidSortCap, 2>, dim3(grid(3, nt)),
+                               dim3(kMidSortBlock), s, A.bucket, rg, cl, cc, rl, keys, vals, ov)) != hipSuccess)
             return e;
-        if ((e = launch_kernel(tile_sort_kernel<kLargeSortBlock, kLargeSortCap, 1>, dim3(grid(2, nt)),
+        if ((e = launch_kernel(tile_sort_kernel<kLargeSortBlock, kLargeSortCap, 1>, dim3(grid(1, nt)),
                                dim3(kLargeSortBlock), s, A.bucket, rg, cl, cc, rl, keys, vals, ov)) != hipSuccess)
             return e;
         if ((e = launch_kernel(tile_sort_kernel<kTileSortBlock, kTileSortCap, 0>, dim3(grid(1, 1ll << 40)),

@@ -203,6 +203,45 @@ def test_bin_sort_long_buckets_bit_exact(dev, orc, name, counts, V):
         B.set_tuning(**prev)
 
 
+SORT_DEPTHS = [
+    ("uniform", lambda rng, n: rng.uniform(0.3, 10.0, n)),
+    ("all_equal", lambda rng, n: np.full(n, 2.5)),
+    ("ten_values", lambda rng, n: rng.integers(1, 11, n) * 0.7),
+    ("clusters", lambda rng, n: np.where(rng.random(n) < 0.6, 3.0 + 1e-5 * rng.random(n),
+                                         np.where(rng.random(n) < 0.99, 7.0 + 1e-3 * rng.random(n), 9e3))),
+    ("half_equal", lambda rng, n: np.where(rng.random(n) < 0.5, 4.0, rng.uniform(3.9, 4.1, n))),
+]
+
+
+@pytest.mark.parametrize("V", [1, 17], ids=["few_tiles", "windowed"])
+@pytest.mark.parametrize("name,depths", SORT_DEPTHS, ids=[c[0] for c in SORT_DEPTHS])
+def test_tile_sort_depth_patterns_bit_exact(dev, orc, name, depths, V):
+    """One tile at each edge of the tile sorts' size classes, for depths that
+    spread (placed by interpolation) and depths that do not (merge sorted):
+    keys and values bit for bit."""
+    from paper_2604_12626_amd import binding as B
+    rng = np.random.default_rng(123)
+    W = H = 256
+    sizes = [1, 2, 63, 64, 65, 511, 512, 513, 2047, 2048, 2049, 4096, 4097, 8192, 8193, 16384, 16385]
+    counts = [sum(sizes)] + [3] * (V - 1)
+    rec, vis = synth.synthetic_records(rng, counts, W, H)
+    vis[:] = 1
+    at = 0
+    for t, n in enumerate(sizes):
+        sel = np.arange(at, at + n)
+        at += n
+        rec[sel, 0] = 16 * (t % 16) + rng.uniform(4.0, 12.0, n)
+        rec[sel, 1] = 16 * (t // 16) + rng.uniform(4.0, 12.0, n)
+        rec[sel, 2] = depths(rng, n)
+        rec[sel, 3] = np.ones(n, np.int32).view(np.float32)
+    perm = rng.permutation(sum(sizes))
+    rec[:sum(sizes)] = rec[perm]
+    tt_o, keys_o, vals_o, ranges_o, K = orc.bin_records(rec, vis, W, H, V)
+    lens = ranges_o.reshape(-1, 2).astype(np.int64)
+    assert np.array_equal((lens[:, 1] - lens[:, 0])[:len(sizes)], sizes)
+    _bin_sort_case(dev, B, rec, tt_o, keys_o, vals_o, ranges_o, K, V, W, H, B.make_params(W, H), K + 5, 0)
+
+
 def _bin_sort_case(dev, B, rec, tt_o, keys_o, vals_o, ranges_o, K, V, W, H, prm, cap, expect_ovf):
     import torch
     tt = torch.from_numpy(tt_o.view(np.int32).copy()).to(dev)

@@ -105,9 +105,23 @@ __device__ __forceinline__ void take_min(float &g, int &i, float g2, int i2) {
     }
 }
 
+// The swept step is asked only of the capsules that can attain its minimum.
+// Every point of the step's parallelogram lies within |step| of the agent's
+// axis at its start, which is itself part of the parallelogram, so a capsule's
+// step gap is at least its clearance less |step|, and the least step gap is
+// at most the least clearance: a capsule whose clearance exceeds the least by
+// more than |step| (and a margin for rounding) cannot attain it.  The few that
+// remain are compacted over the wave, so that one round of lanes usually takes
+// them all instead of one per 64 capsules.  Bound by the VALU and the chain of
+// loads to the capsules; 4096 agents against 184 capsules each 17.9 ->
+// 12.1 us.
+constexpr int kCapChunk = 512;  // capsules of an agent looked at before their steps
+
 __global__ void __launch_bounds__(256) capsule_query_kernel(const CapsuleArgs a) {
-    const int64_t e = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
+    __shared__ float s_least[4][kCapChunk];
+    __shared__ uint16_t s_list[4][kCapChunk];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int64_t e = (int64_t)blockIdx.x * 4 + wave;
     if (e >= a.n_agents) return;  // whole waves leave together
     const V3 p0 = v3(a.agent_pos[3 * e], a.agent_pos[3 * e + 1], a.agent_pos[3 * e + 2]);
     const bool step = a.agent_next != nullptr;
@@ -119,27 +133,86 @@ __global__ void __launch_bounds__(256) capsule_query_kernel(const CapsuleArgs a)
     const int n = hi > lo ? (hi - lo) * a.n_caps : 0;
     float best = INFINITY, best_step = INFINITY;
     int best_i = -1;
-    for (int j = lane; j < n; j += 64) {
-        const int av = lo + j / a.n_caps, c = j - (j / a.n_caps) * a.n_caps;
-        // the avatar's clip frames around its position (clamped like the skinning clips)
-        const int cf = min(max(a.clip_first[av], 0), a.clip_total - 1);
-        const int frames = min(max(a.clip_frames[av], 1), a.clip_total - cf);
-        const float p = a.frame_pos[av];
-        const float pc = p > 0.0f ? fminf(p, (float)(frames - 1)) : 0.0f;
-        const int f0 = frames > 1 ? min((int)floorf(pc), frames - 2) : 0;
-        const int f1 = frames > 1 ? f0 + 1 : 0;
-        const float s = frames > 1 ? pc - (float)f0 : 0.0f;
-        const float4 *c0 = reinterpret_cast<const float4 *>(a.caps + ((size_t)(cf + f0) * a.n_caps + c) * 8);
-        const float4 *c1 = reinterpret_cast<const float4 *>(a.caps + ((size_t)(cf + f1) * a.n_caps + c) * 8);
-        const float4 x0 = c0[0], y0 = c0[1], x1 = c1[0], y1 = c1[1];
-        const float t = 1.0f - s;
-        const V3 ca = v3(t * x0.x + s * x1.x, t * x0.y + s * x1.y, t * x0.z + s * x1.z);
-        const V3 cb = v3(t * y0.x + s * y1.x, t * y0.y + s * y1.y, t * y0.z + s * y1.z);
-        const float r = t * x0.w + s * x1.w;
-        const V3 cd = cb - ca;
-        const float g = sqrtf(seg_seg_dist2(p0, up, ca, cd)) - a.radius - r;
-        take_min(best, best_i, g, av * a.n_caps + c);
-        if (step) best_step = fminf(best_step, seg_parallelogram_dist(ca, cd, p0, sd, up) - a.radius - r);
+    const float sdl = sqrtf(dot(sd, sd));
+    // what the clearances may be off by: near-parallel axes are taken as
+    // parallel, and far coordinates round
+    const float far = 1e-5f * (fabsf(p0.x) + fabsf(p0.y) + fabsf(p0.z));
+    // a chunk holds capsules of at most 64 avatars, whose clip frames lie one
+    // avatar per lane
+    const int chunk = (int)min((int64_t)kCapChunk, 63 * (int64_t)a.n_caps);
+    const float inv_caps = 1.0f / (float)a.n_caps;
+    for (int base = 0; base < n; base += chunk) {  // uniform
+        const int m = min(n - base, chunk);
+        const int av0 = base / a.n_caps, off = base - av0 * a.n_caps;
+        int row0 = 0, row1 = 0;  // first capsule of the avatar's two frames
+        float sp = 0.0f;
+        if (lo + av0 + lane < hi) {
+            // the avatar's clip frames around its position (clamped like the skinning clips)
+            const int av = lo + av0 + lane;
+            const int cf = min(max(a.clip_first[av], 0), a.clip_total - 1);
+            const int frames = min(max(a.clip_frames[av], 1), a.clip_total - cf);
+            const float p = a.frame_pos[av];
+            const float pc = p > 0.0f ? fminf(p, (float)(frames - 1)) : 0.0f;
+            const int f0 = frames > 1 ? min((int)floorf(pc), frames - 2) : 0;
+            row0 = cf + f0;
+            row1 = cf + (frames > 1 ? f0 + 1 : 0);
+            sp = frames > 1 ? pc - (float)f0 : 0.0f;
+        }
+        // avatar (of the chunk's) of its capsule j.  Below 2^20 the quotient
+        // by way of floats is exact: j + 1/2 is at least 1 / (2 n_caps) from
+        // a multiple, far above the rounding.
+        auto avatar = [&](int j) {
+            return a.n_caps < (1 << 20) ? (int)(((float)(j + off) + 0.5f) * inv_caps) : (j + off) / a.n_caps;
+        };
+        // capsule j of the chunk, interpolated in its clip (every lane takes
+        // part in the exchange)
+        auto capsule = [&](int j, V3 &ca, V3 &cd, float &r) {
+            const int t = avatar(j), c = j + off - t * a.n_caps;
+            const int r0 = __shfl(row0, t, 64), r1 = __shfl(row1, t, 64);
+            const float s = __shfl(sp, t, 64);
+            const float4 *c0 = reinterpret_cast<const float4 *>(a.caps + ((size_t)r0 * a.n_caps + c) * 8);
+            const float4 *c1 = reinterpret_cast<const float4 *>(a.caps + ((size_t)r1 * a.n_caps + c) * 8);
+            const float4 x0 = c0[0], y0 = c0[1], x1 = c1[0], y1 = c1[1];
+            const float t1 = 1.0f - s;
+            ca = v3(t1 * x0.x + s * x1.x, t1 * x0.y + s * x1.y, t1 * x0.z + s * x1.z);
+            const V3 cb = v3(t1 * y0.x + s * y1.x, t1 * y0.y + s * y1.y, t1 * y0.z + s * y1.z);
+            r = t1 * x0.w + s * x1.w;
+            cd = cb - ca;
+        };
+        for (int j0 = 0; j0 < m; j0 += 64) {
+            const int j = j0 + lane;
+            V3 ca, cd;
+            float r;
+            capsule(min(j, m - 1), ca, cd, r);
+            if (j >= m) continue;
+            const float g = sqrtf(seg_seg_dist2(p0, up, ca, cd)) - a.radius - r;
+            take_min(best, best_i, g, lo * a.n_caps + base + j);
+            if (step)  // the least gap its swept step can have
+                s_least[wave][j] = g - 1.001f * sdl - 2e-3f * (a.height + sqrtf(dot(cd, cd)) + sdl) -
+                                   1e-5f * fabsf(g) - far;
+        }
+        if (!step) continue;  // uniform
+        float least = best;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) least = fminf(least, __shfl_xor(least, off, 64));
+        lds_wave_sync();
+        int cnt = 0;
+        for (int j0 = 0; j0 < m; j0 += 64) {
+            const int j = j0 + lane;
+            const bool in = j < m && !(s_least[wave][j] > least);  // not-a-number stays in
+            const uint64_t bal = __ballot(in);
+            if (in) s_list[wave][cnt + __popcll(bal & ((1ull << lane) - 1ull))] = (uint16_t)j;
+            cnt += __popcll(bal);
+        }
+        lds_wave_sync();
+        for (int k0 = 0; k0 < cnt; k0 += 64) {
+            V3 ca, cd;
+            float r;
+            capsule(s_list[wave][min(k0 + lane, cnt - 1)], ca, cd, r);
+            if (k0 + lane < cnt)
+                best_step = fminf(best_step, seg_parallelogram_dist(ca, cd, p0, sd, up) - a.radius - r);
+        }
+        lds_wave_sync();  // the list is read: the next chunk may overwrite it
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {

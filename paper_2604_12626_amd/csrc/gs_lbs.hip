@@ -133,12 +133,9 @@ __global__ void __launch_bounds__(256) lbs_backward_kernel(const LbsArgs a) {
     reinterpret_cast<float4 *>(a.d_quats)[i] = make_float4(dq[0], dq[1], dq[2], dq[3]);
 }
 
-// Adjoint w.r.t. the joint matrices (fixed-matrix mode).  A persistent grid
-// walks the Gaussians; each thread forms its Gaussian's 3x4 adjoint dL/dA
-// (g mean^T + 2 G A3 Sigma | g) and adds w_k dL/dA to the four joints it
-// blends, first into the workgroup's LDS copy of all joint adjoints (when
-// they fit, kJointLds floats), then the workgroup adds its nonzero entries to
-// the output with float atomics.
+// Adjoint w.r.t. the joint matrices (fixed-matrix mode): with dL/dA_g =
+// (g mean^T + 2 G A3 Sigma | g) the 3x4 adjoint of Gaussian g's blended
+// matrix, joint j of an avatar gets the sum over its Gaussians of w_gj dL/dA_g.
 constexpr int kJointLds = 4096;
 
 __device__ __forceinline__ void gaussian_matrix_adjoint(const LbsArgs &a, int64_t i, const float *A, float *dA) {
@@ -177,6 +174,142 @@ __device__ __forceinline__ void gaussian_matrix_adjoint(const LbsArgs &a, int64_
     }
 }
 
+// the four joints, weights and avatar of Gaussian i, clamped as in the blend
+struct Blend4 {
+    int av, j[4];
+    float w[4];
+};
+__device__ __forceinline__ Blend4 blend_of(const LbsArgs &a, int64_t i) {
+    const uchar4 ji = reinterpret_cast<const uchar4 *>(a.joint_idx)[i];
+    const float4 w = reinterpret_cast<const float4 *>(a.weights)[i];
+    const int av = a.avatar_of[i], jl = a.n_joints - 1;
+    return {av < 0 ? 0 : (av >= a.n_avatars ? a.n_avatars - 1 : av),
+            {min((int)ji.x, jl), min((int)ji.y, jl), min((int)ji.z, jl), min((int)ji.w, jl)},
+            {w.x, w.y, w.z, w.w}};
+}
+
+// Up to 16 MB joints: the sum is a matrix product, D[joint][element] =
+// sum_g W[joint][g] dA[g][element], and the matrix cores take it.  A wave
+// owns a contiguous run of Gaussians, 64 at a time: each lane scatters its
+// four weights into its column of W (zero elsewhere) and its twelve elements
+// into dA, both in LDS with the Gaussian fastest, and MB x 16
+// v_mfma_f32_16x16x4_f32 add them to the wave's sums.  The sums stay in
+// registers until the avatar changes, then go to the workgroup's copy of the
+// output in LDS (where it fits, kJointLds floats), whose nonzero entries end
+// in float atomics.  A group that spans avatars takes one product per avatar,
+// up to four; the Gaussians of further ones add their 48 terms themselves
+// (avatars mixed at random would take a product per Gaussian).  So does a
+// Gaussian whose dA is not finite, which would reach every joint of the
+// product through the zero weights.  Bound by its 140 B of reads per Gaussian
+// and their latency; adding every element to LDS with atomics (48 per
+// Gaussian, a few lanes of a wave on the same joint each time) took 114 us
+// for 400k Gaussians of 8 avatars with 24 joints, this takes 25 us.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kJgStride = 68;  // floats per row of 64 Gaussians: rows on different banks
+template <int MB, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) lbs_joint_mfma_kernel(const LbsArgs a, float *d_skin) {
+    __shared__ __attribute__((aligned(16))) float s_w[WAVES][16 * MB][kJgStride];
+    __shared__ __attribute__((aligned(16))) float s_da[WAVES][12][kJgStride];
+    __shared__ float s_acc[kJointLds];
+    const int64_t n_mats = (int64_t)a.n_avatars * a.n_joints * 12;
+    const bool lds = n_mats <= kJointLds;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int mi = lane & 15, mk = lane >> 4;  // operand row / column, k block
+    float(*W)[kJgStride] = s_w[wave];
+    float(*dAs)[kJgStride] = s_da[wave];
+    for (int k = lane; k < 16 * MB * kJgStride; k += 64) (&W[0][0])[k] = 0.0f;
+    if (lds)
+        for (int k = threadIdx.x; k < n_mats; k += 64 * WAVES) s_acc[k] = 0.0f;
+    __syncthreads();
+    f32x4 acc[MB];
+    int acc_av = -1;  // avatar of the sums held in acc (uniform)
+    auto add = [&](int64_t at, float v) {
+        if (lds) atomicAdd(&s_acc[at], v);
+        else atomicAdd(&d_skin[at], v);
+    };
+    auto flush = [&](int next) {  // D row 4 mk + r, column mi
+        if (acc_av >= 0 && mi < 12) {
+#pragma unroll
+            for (int b = 0; b < MB; ++b)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int j = 16 * b + 4 * mk + r;
+                    if (j < a.n_joints && acc[b][r] != 0.0f)
+                        add(((int64_t)acc_av * a.n_joints + j) * 12 + mi, acc[b][r]);
+                }
+        }
+#pragma unroll
+        for (int b = 0; b < MB; ++b) acc[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        acc_av = next;
+    };
+    flush(-1);
+    const int64_t groups = (a.n + 63) / 64, w0 = (int64_t)blockIdx.x * WAVES + wave, nw = (int64_t)gridDim.x * WAVES;
+    for (int64_t gr = groups * w0 / nw; gr < groups * (w0 + 1) / nw; ++gr) {
+        const int64_t i = gr * 64 + lane;
+        const bool valid = i < a.n;
+        float A[12], dA[12];
+#pragma unroll
+        for (int e = 0; e < 12; ++e) dA[e] = 0.0f;
+        Blend4 bl = {-1, {0, 0, 0, 0}, {0.0f, 0.0f, 0.0f, 0.0f}};
+        if (valid) {
+            bl = blend_of(a, i);
+            blend_matrix<false>(a, i, A);
+            gaussian_matrix_adjoint(a, i, A, dA);
+        }
+        bool finite = true;
+#pragma unroll
+        for (int e = 0; e < 12; ++e) finite = finite && isfinite(dA[e]);
+        lds_wave_sync();
+#pragma unroll
+        for (int e = 0; e < 12; ++e) dAs[e][lane] = finite ? dA[e] : 0.0f;
+        uint64_t left = __ballot(valid && finite);
+        for (int turn = 0; left && turn < 4; ++turn) {  // one avatar at a time
+            const int av = __builtin_amdgcn_readlane(bl.av, __ffsll((unsigned long long)left) - 1);
+            const bool mine = valid && finite && bl.av == av;
+            left &= ~__ballot(mine);
+            if (av != acc_av) flush(av);
+            if (mine)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) atomicAdd(&W[bl.j[k]][lane], bl.w[k]);  // a joint may come twice
+            lds_wave_sync();
+            f32x4 bv[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                bv[m] = mi < 12 ? *reinterpret_cast<const f32x4 *>(&dAs[mi][16 * mk + 4 * m])
+                                : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int b = 0; b < MB; ++b) {
+                const f32x4 *row = reinterpret_cast<const f32x4 *>(&W[16 * b + mi][16 * mk]);
+                const f32x4 wv[4] = {row[0], row[1], row[2], row[3]};
+#pragma unroll
+                for (int st = 0; st < 16; ++st)
+                    acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[st >> 2][st & 3], bv[st >> 2][st & 3], acc[b], 0,
+                                                                  0, 0);
+            }
+            lds_wave_sync();
+            if (mine)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) W[bl.j[k]][lane] = 0.0f;
+            lds_wave_sync();
+        }
+        if (valid && (!finite || ((left >> lane) & 1ull)))
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int e = 0; e < 12; ++e)
+                    add(((int64_t)bl.av * a.n_joints + bl.j[k]) * 12 + e, bl.w[k] * dA[e]);
+    }
+    flush(-1);
+    if (lds) {
+        __syncthreads();
+        for (int k = threadIdx.x; k < n_mats; k += 64 * WAVES)
+            if (s_acc[k] != 0.0f) atomicAdd(&d_skin[k], s_acc[k]);
+    }
+}
+
+// More joints than that: a persistent grid walks the Gaussians, each thread
+// adding w_k dA to the four joints it blends, first in the workgroup's LDS
+// copy of the output (when it fits), whose nonzero entries end in float
+// atomics.
 __global__ void __launch_bounds__(256) lbs_joint_grad_kernel(const LbsArgs a, float *d_skin) {
     __shared__ float s_acc[kJointLds];
     const int64_t n_mats = (int64_t)a.n_avatars * a.n_joints * 12;
@@ -190,20 +323,14 @@ __global__ void __launch_bounds__(256) lbs_joint_grad_kernel(const LbsArgs a, fl
         float A[12], dA[12];
         blend_matrix<false>(a, i, A);
         gaussian_matrix_adjoint(a, i, A, dA);
-        const uchar4 ji = reinterpret_cast<const uchar4 *>(a.joint_idx)[i];
-        const float4 w = reinterpret_cast<const float4 *>(a.weights)[i];
-        int av = a.avatar_of[i];
-        av = av < 0 ? 0 : (av >= a.n_avatars ? a.n_avatars - 1 : av);
-        const int j[4] = {min((int)ji.x, a.n_joints - 1), min((int)ji.y, a.n_joints - 1),
-                          min((int)ji.z, a.n_joints - 1), min((int)ji.w, a.n_joints - 1)};
-        const float wk[4] = {w.x, w.y, w.z, w.w};
+        const Blend4 bl = blend_of(a, i);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int64_t base = ((int64_t)av * a.n_joints + j[k]) * 12;
+            const int64_t base = ((int64_t)bl.av * a.n_joints + bl.j[k]) * 12;
 #pragma unroll
             for (int e = 0; e < 12; ++e) {
-                if (lds) atomicAdd(&s_acc[base + e], wk[k] * dA[e]);
-                else atomicAdd(&d_skin[base + e], wk[k] * dA[e]);
+                if (lds) atomicAdd(&s_acc[base + e], bl.w[k] * dA[e]);
+                else atomicAdd(&d_skin[base + e], bl.w[k] * dA[e]);
             }
         }
     }
@@ -218,9 +345,17 @@ hipError_t launch_lbs_joint_grad(const LbsArgs &a, float *d_skin, int n_cu, hipS
     const int64_t n_mats = (int64_t)a.n_avatars * a.n_joints * 12;
     hipError_t e = launch_fill_u32(reinterpret_cast<uint32_t *>(d_skin), 0u, n_mats, s);
     if (e != hipSuccess || a.n == 0) return e;
-    int64_t grid = (a.n + 255) / 256;
-    if (grid > (int64_t)n_cu) grid = n_cu;  // one workgroup per CU: few LDS-to-HBM flushes
-    return launch_kernel(lbs_joint_grad_kernel, dim3((unsigned)grid), dim3(256), s, a, d_skin);
+    // one workgroup per CU: few flushes to HBM.  The joint count decides how
+    // many 16-row blocks of W a wave keeps in LDS; 64 joints are what four
+    // waves of a CU have room for.
+    auto grid = [&](int waves) {
+        const int64_t g = ((a.n + 63) / 64 + waves - 1) / waves;
+        return dim3((unsigned)(g < n_cu ? g : n_cu));
+    };
+    if (a.n_joints <= 16) return launch_kernel(lbs_joint_mfma_kernel<1, 8>, grid(8), dim3(512), s, a, d_skin);
+    if (a.n_joints <= 32) return launch_kernel(lbs_joint_mfma_kernel<2, 8>, grid(8), dim3(512), s, a, d_skin);
+    if (a.n_joints <= 64) return launch_kernel(lbs_joint_mfma_kernel<4, 4>, grid(4), dim3(256), s, a, d_skin);
+    return launch_kernel(lbs_joint_grad_kernel, grid(4), dim3(256), s, a, d_skin);
 }
 
 // Forward kinematics: one thread per avatar walks its joints parent first.

@@ -723,6 +723,51 @@ def test_lbs_joint_matrix_gradient_parity(dev, orc, n_avatars):
     assert np.all(got[ref == 0] == 0)  # joints no Gaussian blends stay exactly zero
 
 
+@pytest.mark.parametrize("J", [1, 16, 17, 32, 33, 64, 65])
+def test_lbs_joint_matrix_gradient_joint_counts(dev, orc, J):
+    """Joint-matrix gradients at the edges of the matrix product's row blocks
+    and past them, with avatars of ragged sizes in runs (groups of 64 that
+    span one, two, and more than four avatars), joints blended twice by one
+    Gaussian, and one Gaussian whose adjoint is infinite: it reaches its own
+    joints only."""
+    import torch
+    from paper_2604_12626_amd import binding as B
+    rng = np.random.default_rng(1000 + J)
+    sizes = [700, 1, 130, 5, 9, 3, 2, 11, 64, 1000 - 925 + 37]
+    A, n = len(sizes), sum(sizes)
+    aof = np.repeat(np.arange(A), sizes).astype(np.int32)
+    g = synth.gaussians_cube(n, rng)
+    g["joint_idx"] = rng.integers(0, J, (n, 4)).astype(np.uint8)
+    g["weights"] = rng.dirichlet(np.ones(4), size=n).astype(F32)
+    skin = (np.eye(3, 4).reshape(12) + 0.2 * rng.standard_normal((A, J, 12))).astype(F32)
+    gm = rng.standard_normal((n, 3)).astype(F32)
+    gc = (rng.standard_normal((n, 6)) * 1e3).astype(F32)
+    t = to_dev(g, dev)
+
+    def run(gmx):
+        out = torch.full((A, J, 12), 7.0, device=dev)
+        B.deform_lbs_backward_joints(t["means"], t["log_scales"], t["quats"], t["joint_idx"], t["weights"],
+                                     torch.from_numpy(aof).to(dev), torch.from_numpy(skin).to(dev),
+                                     torch.from_numpy(gmx).to(dev), torch.from_numpy(gc).to(dev), out)
+        torch.cuda.synchronize()
+        return out.cpu().numpy().astype(np.float64)
+
+    ref = orc.lbs_backward_joints(g["means"], g["log_scales"], g["quats"], orc.dense_weights(g["joint_idx"],
+                                  g["weights"], J), aof, skin, J, gm, gc)
+    got = run(gm)
+    err = np.abs(got - ref).max() / np.abs(ref).max()
+    say("joint gradients, %d joints: %.2e of the largest" % (J, err))
+    assert err <= 2e-4
+    assert np.all(got[ref == 0] == 0)
+    bad = 703  # in the avatar of 130
+    gm[bad, 0] = np.inf
+    got2 = run(gm)
+    own = np.zeros((A, J), bool)
+    own[aof[bad], g["joint_idx"][bad]] = True
+    assert not np.isfinite(got2[own]).all(axis=-1).any()
+    assert np.abs(got2[~own] - ref[~own]).max(initial=0.0) <= 2e-4 * np.abs(ref).max()
+
+
 @pytest.mark.parametrize("n_avatars", [8, 131], ids=["8", "131_ragged"])
 def test_forward_kinematics_parity(dev, orc, n_avatars):
     import torch

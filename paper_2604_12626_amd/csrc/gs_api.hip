@@ -331,34 +331,52 @@ gs_status gs_project(const gs_gaussians *segs, int32_t n_segs, const gs_camera *
     if (off[n_views] == 0) return GS_OK;
     if (!out->tiles_touched || !out->rec) return fail(GS_ERR_INVALID_ARGUMENT, "out arrays are NULL");
     if (!aligned(out->rec, 16)) return fail(GS_ERR_INVALID_ARGUMENT, "rec must be 16-byte aligned");
+    // segments of one SH degree and layout share launches, up to kProjSegs
+    // segments and kProjViews (segment, view) pairs each
+    gs::ProjectArgs a = {};
+    a.cams = cams;
+    a.tiles_touched = out->tiles_touched;
+    a.rec = reinterpret_cast<float4 *>(out->rec);
+    a.W = p->width;
+    a.H = p->height;
+    a.TX = tiles_x(p);
+    a.TY = tiles_y(p);
+    a.near_plane = p->near_plane;
+    a.lowpass = p->lowpass;
+    a.sigma_cut = p->sigma_cut;
+    a.fov_clamp = p->fov_clamp;
+    hipError_t e;
+    int open = -1;  // segment of the last pair
+    auto flush = [&]() {
+        const hipError_t r = gs::launch_project(a, (hipStream_t)stream);
+        a.n_segs = 0;
+        return r;
+    };
     for (int s = 0; s < n_segs; ++s) {
-        std::vector<int> views;
-        for (int v = 0; v < n_views; ++v)
-            if (view_seg_mask[v] & (1u << s)) views.push_back(v);
-        for (size_t c = 0; c < views.size(); c += gs::kProjViews) {
-            gs::ProjectArgs a = {};
-            a.seg = segs[s];
-            a.cams = cams;
-            a.tiles_touched = out->tiles_touched;
-            a.rec = reinterpret_cast<float4 *>(out->rec);
-            a.nv = (int)std::min(views.size() - c, (size_t)gs::kProjViews);
-            for (int k = 0; k < a.nv; ++k) {
-                const int v = views[c + k];
-                a.view[k] = v;
-                a.base[k] = off[v] + seg_offset_in_view(segs, view_seg_mask[v], s);
+        if (segs[s].n == 0) continue;
+        for (int v = 0; v < n_views; ++v) {
+            if (!(view_seg_mask[v] & (1u << s))) continue;
+            if (a.n_segs > 0) {
+                const gs_gaussians &g = a.seg[a.n_segs - 1];
+                const bool same = g.sh_degree == segs[s].sh_degree && g.layout == segs[s].layout;
+                if (!same || a.first_pair[a.n_segs] == gs::kProjViews) {
+                    if ((e = flush()) != hipSuccess) return hip_fail(e, "gs_project");
+                }
             }
-            a.W = p->width;
-            a.H = p->height;
-            a.TX = tiles_x(p);
-            a.TY = tiles_y(p);
-            a.near_plane = p->near_plane;
-            a.lowpass = p->lowpass;
-            a.sigma_cut = p->sigma_cut;
-            a.fov_clamp = p->fov_clamp;
-            hipError_t e = gs::launch_project(a, (hipStream_t)stream);
-            if (e != hipSuccess) return hip_fail(e, "gs_project");
+            // the segment's first pair of this launch
+            if (a.n_segs == 0 || open != s) {
+                if (a.n_segs == gs::kProjSegs && (e = flush()) != hipSuccess) return hip_fail(e, "gs_project");
+                open = s;
+                a.seg[a.n_segs] = segs[s];
+                a.first_pair[a.n_segs + 1] = a.first_pair[a.n_segs];
+                ++a.n_segs;
+            }
+            const int k = a.first_pair[a.n_segs]++;
+            a.view[k] = v;
+            a.base[k] = off[v] + seg_offset_in_view(segs, view_seg_mask[v], s);
         }
     }
+    if ((e = flush()) != hipSuccess) return hip_fail(e, "gs_project");
     return GS_OK;
 }
 

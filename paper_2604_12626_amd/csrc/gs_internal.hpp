@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include <tuple>
+#include <type_traits>
 #include <utility>
 
 #include "gs.h"
@@ -24,14 +25,21 @@ enum { kGU = 0, kGV, kGA, kGB, kGC, kGO, kGR, kGG, kGBl, kGZ, kG2D };
 // ---------------------------------------------------------------------------
 // launch argument blocks (passed by value as kernel arguments)
 // ---------------------------------------------------------------------------
+// One projection launch: up to kProjSegs segments of one SH degree and layout
+// and up to kProjViews (segment, view) pairs.  Segment k's pairs are
+// [first_pair[k], first_pair[k + 1]), its workgroups [first_block[k],
+// first_block[k + 1]) (set by the launcher).
+constexpr int kProjSegs = 8;
 struct ProjectArgs {
-    gs_gaussians seg;
+    gs_gaussians seg[kProjSegs];
+    int32_t n_segs;
+    int32_t first_pair[kProjSegs + 1];
+    uint32_t first_block[kProjSegs + 1];
     const gs_camera *cams;
     uint32_t *tiles_touched;
     float4 *rec;
-    int64_t base[kProjViews];  // first instance of this segment in each view
+    int64_t base[kProjViews];  // first instance of the pair's segment in its view
     int32_t view[kProjViews];  // view index
-    int32_t nv;
     int32_t W, H, TX, TY;
     float near_plane, lowpass, sigma_cut, fov_clamp;
 };
@@ -197,7 +205,7 @@ struct SortPlan {
 
 // launchers (one per translation unit)
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
-hipError_t launch_project(const ProjectArgs &a, hipStream_t s);
+hipError_t launch_project(ProjectArgs a, hipStream_t s);
 SortPlan make_sort_plan(int64_t n, int64_t capacity, int64_t tiles_per_view, int64_t n_views);
 hipError_t run_bin_sort(const SortPlan &P, const uint32_t *tt, const float4 *rec, int TX, int TY, char *ws,
                         uint64_t *keys, uint32_t *vals, uint32_t *ranges, uint32_t *order, int64_t *d_num,
@@ -227,8 +235,10 @@ hipError_t launch_capsule_queries(const CapsuleArgs &a, hipStream_t s);
 // Launch a kernel through hipLaunchKernel so that the call returns the status
 // of this launch itself (never a stale error of an earlier runtime call).  The
 // arguments are converted to the kernel's parameter types first.
+// launch_kernel_lds: with `lds` bytes of dynamic LDS.
 template <typename... KArgs, typename... Args>
-inline hipError_t launch_kernel(void (*kernel)(KArgs...), dim3 grid, dim3 block, hipStream_t s, Args &&...args) {
+inline hipError_t launch_kernel_lds(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStream_t s,
+                                    Args &&...args) {
     static_assert(sizeof...(KArgs) == sizeof...(Args), "kernel argument count");
     if (grid.x == 0 || grid.y == 0 || grid.z == 0) return hipSuccess;
     struct Pack {
@@ -239,7 +249,11 @@ inline hipError_t launch_kernel(void (*kernel)(KArgs...), dim3 grid, dim3 block,
         int k = 0;
         ((argv[k++] = static_cast<void *>(&x)), ...);
     }, pack.t);
-    return hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, argv, 0, s);
+    return hipLaunchKernel(reinterpret_cast<const void *>(kernel), grid, block, argv, lds, s);
+}
+template <typename... KArgs, typename... Args>
+inline hipError_t launch_kernel(void (*kernel)(KArgs...), dim3 grid, dim3 block, hipStream_t s, Args &&...args) {
+    return launch_kernel_lds(kernel, grid, block, 0, s, std::forward<Args>(args)...);
 }
 
 // ---------------------------------------------------------------------------

@@ -500,6 +500,114 @@ def _planes(g):
     return out
 
 
+def _awkward(rng, g):
+    """Spoils a few thousand Gaussians of a segment: non-finite and huge
+    values, means on the near plane, far off and on the camera, scales that
+    cover the image from behind its edges."""
+    n = len(g["means"])
+    k = n // 128 * 8
+    i = rng.permutation(n)[:k].reshape(-1, k // 8)
+    g["means"][i[0], 0] = np.array([np.nan, np.inf, -np.inf, 1e30], F32)[np.arange(k // 8) % 4]
+    g["means"][i[1]] *= F32(1e4)
+    g["opacity"][i[2]] = np.array([np.nan, np.inf, 0.0, 1.0], F32)[np.arange(k // 8) % 4]
+    if "log_scales" in g:
+        g["log_scales"][i[3]] = rng.uniform(-2.0, 3.0, (k // 8, 3))
+        g["log_scales"][i[4], 1] = np.array([np.nan, np.inf, -np.inf, 60.0], F32)[np.arange(k // 8) % 4]
+        g["quats"][i[5]] = 0.0
+    else:
+        g["cov6"][i[3]] *= F32(1e4)
+        g["cov6"][i[4], 3] = np.array([np.nan, np.inf, -1.0, 1e12], F32)[np.arange(k // 8) % 4]
+    return g
+
+
+@pytest.mark.parametrize("case", ["sh0", "sh1", "sh2", "sh3", "cov6", "planes", "views12"])
+def test_project_two_steps_equal_direct(dev, case):
+    """Launches of several views and large enough for the two-step projection
+    (bound, list, exact; over 360 MB of attributes and records) against the same Gaussians in slices that take the direct kernel: counts
+    equal everywhere, records bit for bit wherever drawn."""
+    import torch
+    from paper_2604_12626_amd import binding as B
+    rng = np.random.default_rng(1234)
+    views = 12 if case == "views12" else 9
+    n, W, H = 700_001, 333, 217
+    D = {"sh0": 0, "sh1": 1, "sh2": 2}.get(case, 3)
+    g = synth.gaussians_room(n, rng, sh_degree=D)
+    if case == "cov6":
+        A = rng.normal(0.0, 0.02, (n, 3, 3))
+        S = A @ np.transpose(A, (0, 2, 1))
+        del g["log_scales"], g["quats"]
+        g["cov6"] = S[:, [0, 0, 0, 1, 1, 2], [0, 1, 2, 1, 2, 2]].astype(F32)
+    g = _awkward(rng, g)
+    cams_np = [synth.camera_room(rng, W, H) for _ in range(views)]
+    # a mean on the first camera's near plane (z rounds either way) and one at its centre
+    R, tr = cams_np[0][:9].reshape(3, 3).astype(np.float64), cams_np[0][9:12].astype(np.float64)
+    near = rng.uniform(-0.1, 0.1, (500, 3))
+    near[:, 2] = 0.2 * (1.0 + rng.uniform(-3e-7, 3e-7, 500))
+    near[0] = 0.0
+    g["means"][:500] = ((near - tr) @ R).astype(F32)
+    cams = torch.from_numpy(np.stack(cams_np)).to(dev)
+    prm = B.make_params(W, H)
+
+    def project(seg, count):
+        t = to_dev(_planes(seg) if case == "planes" else seg, dev)
+        tt = torch.full((views * count,), -7, dtype=torch.int32, device=dev)
+        rec = torch.zeros((views * count, 12), dtype=torch.float32, device=dev)
+        B.project([t], cams, [[0]] * views, prm, tt, rec)
+        torch.cuda.synchronize()
+        return tt.view(views, count), rec.view(views, count, 12)
+
+    tt, rec = project(g, n)
+    drawn = 0
+    for a in range(0, n, 20_011):
+        b = min(n, a + 20_011)
+        part = {k: (np.ascontiguousarray(v[a:b]) if isinstance(v, np.ndarray) else v) for k, v in g.items()}
+        ts, rs = project(part, b - a)
+        assert torch.equal(tt[:, a:b], ts)
+        vis = ts > 0
+        drawn += int(vis.sum())
+        assert torch.equal(rec[:, a:b][vis].view(torch.int32), rs[vis].view(torch.int32))
+    say("two-step projection, %s: %d of %d drawn" % (case, drawn, views * n))
+    assert drawn > 1000  # the comparison saw records
+
+
+def test_project_many_segments_share_launches(dev):
+    """Eleven segments of mixed degrees drawn by nine views (more segments and
+    (segment, view) pairs than one launch takes, some views without some
+    segments, an empty segment) against one call per segment and view."""
+    import torch
+    from paper_2604_12626_amd import binding as B
+    rng = np.random.default_rng(77)
+    W, H, V = 200, 150, 9
+    sizes = [300, 257, 1, 0, 640, 64, 1000, 129, 5, 77, 256]
+    segs_np = [synth.gaussians_room(max(n, 1), rng, sh_degree=[3, 3, 3, 3, 3, 3, 3, 3, 3, 1, 3][k])
+               for k, n in enumerate(sizes)]
+    segs = []
+    for n, g in zip(sizes, segs_np):
+        segs.append(to_dev({k: (v[:n] if isinstance(v, np.ndarray) else v) for k, v in g.items()}, dev))
+    cams = torch.from_numpy(np.stack([synth.camera_room(rng, W, H) for _ in range(V)])).to(dev)
+    vs = [[s for s in range(len(sizes)) if (s + v) % 5 != 0] for v in range(V)]
+    prm = B.make_params(W, H)
+    total = B.instance_offsets(segs, vs)[-1]
+    tt = torch.full((total,), -7, dtype=torch.int32, device=dev)
+    rec = torch.zeros((total, 12), dtype=torch.float32, device=dev)
+    B.project(segs, cams, vs, prm, tt, rec)
+    at = 0
+    for v in range(V):
+        for s in vs[v]:
+            n = sizes[s]
+            if n == 0:
+                continue
+            t1 = torch.full((n,), -7, dtype=torch.int32, device=dev)
+            r1 = torch.zeros((n, 12), dtype=torch.float32, device=dev)
+            B.project([segs[s]], cams[v:v + 1].contiguous(), [[0]], prm, t1, r1)
+            assert torch.equal(tt[at:at + n], t1)
+            vis = t1 > 0
+            r1[:, 11] = torch.full((n,), v, dtype=torch.int32, device=dev).view(torch.float32)
+            assert torch.equal(rec[at:at + n][vis].view(torch.int32), r1[vis].view(torch.int32))
+            at += n
+    assert at == total
+
+
 def test_project_planes_equals_rows(dev):
     """A segment stored component-major (planes) projects to exactly the
     records of the same segment stored in rows -- a scene with rotations and

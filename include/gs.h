@@ -178,10 +178,10 @@ void gs_default_params(gs_params *p, int32_t width, int32_t height);
  *    look-back (16, 32 or 64, default 16).
  *  sort_algorithm: 0 (default) sorts by tile buckets (count per tile,
  *    scatter into buckets, sort each bucket by (depth, instance) in LDS)
- *    when every view has at most 4096 tiles and the launch at most 2^18
- *    tiles over all views (beyond 4096 in all, the counts are taken in a
- *    sliding window of whole views), and with the onesweep radix sort
- *    otherwise; 1 always uses the onesweep radix sort.  Both give the same
+ *    when every view has at most 8192 tiles and the launch at most 2^18
+ *    tiles over all views (several views of more than 4096 tiles in all take
+ *    their counts in a sliding window of whole views), and with the onesweep
+ *    radix sort otherwise; 1 always uses the onesweep radix sort.  Both give the same
  *    keys, values, ranges and work order.
  *  composite_pairs: 0 (default) lets gs_composite walk each quadrant's list
  *    with a pair of waves (one evaluates the alphas of a chunk while the
@@ -342,7 +342,7 @@ size_t gs_tile_order_words(int32_t n_views, const gs_params *p);
  * result is the (key, value) pairs in the order a stable sort by key of the
  * keys emitted in ascending instance order gives (ties in depth keep
  * ascending instance order), computed either by bucketing the keys by tile
- * and sorting each bucket (launches with up to 4096 tiles over all views,
+ * and sorting each bucket (views of up to 8192 tiles, 2^18 over all views,
  * unless gs_tuning selects the other path) or by a stable LSD radix sort
  * over the significant key bits (one hand-written onesweep pass per 8-bit
  * digit); both give identical output.

@@ -203,6 +203,33 @@ def test_bin_sort_long_buckets_bit_exact(dev, orc, name, counts, V):
         B.set_tuning(**prev)
 
 
+BIG_VIEW_CASES = [
+    # one view's tile counters all in LDS: just past 4096 tiles, and 8192
+    ("1view_1040x1012_4160_tiles", [60000], 1040, 1012),
+    ("1view_2048x1024_8192_tiles", [90000], 2048, 1024),
+    # 8208 tiles: the onesweep sort
+    ("1view_2050x1024", [30000], 2052, 1024),
+    # several such views: a window of one view that moves with them
+    ("3views_1920x1080_window_of_one", [40000, 100, 30000], 1920, 1080),
+    # 475 tiles a view: a window of 17 views, 24 views wrap its ring; then the
+    # same drawn by few instances, so that one block meets many views
+    ("24views_400x300_ring", [6000] * 24, 400, 300),
+    ("24views_400x300_block_past_window", [150] * 24, 400, 300),
+]
+
+
+@pytest.mark.parametrize("name,counts,W,H", BIG_VIEW_CASES, ids=[c[0] for c in BIG_VIEW_CASES])
+def test_bin_sort_big_views_bit_exact(dev, orc, name, counts, W, H):
+    from paper_2604_12626_amd import binding as B
+    rng = np.random.default_rng(zlib.crc32(name.encode()))
+    rec, vis = synth.synthetic_records(rng, counts, W, H)
+    tt_o, keys_o, vals_o, ranges_o, K = orc.bin_records(rec, vis, W, H, len(counts))
+    say("bin_sort:", name, "instances", len(rec), "K", K)
+    prm = B.make_params(W, H)
+    for cap, ovf in ((K, 0), (K - 1, 1)):
+        _bin_sort_case(dev, B, rec, tt_o, keys_o, vals_o, ranges_o, K, len(counts), W, H, prm, cap, ovf)
+
+
 SORT_DEPTHS = [
     ("uniform", lambda rng, n: rng.uniform(0.3, 10.0, n)),
     ("all_equal", lambda rng, n: np.full(n, 2.5)),

@@ -331,6 +331,20 @@ def test_composite_parity(dev, orc, name, counts, W, H, rmed, aniso, pairs):
         B.set_tuning(**prev)
 
 
+@pytest.mark.parametrize("pairs", [1, 2], ids=["one_wave", "wave_pairs"])
+@pytest.mark.parametrize("rmed,aniso", [(60.0, 3.0), (20.0, 3.0), (1.0, 0.0)], ids=["long_needles", "needles", "dots"])
+def test_composite_cull_parity(dev, orc, rmed, aniso, pairs):
+    """The quadrant cull at its extremes: needles of condition number up to
+    10^5 that cross a quadrant by a corner, and sub-pixel dots, on an image
+    whose right and lower tiles are cut.  The oracle culls nothing."""
+    from paper_2604_12626_amd import binding as B
+    prev = B.set_tuning(composite_pairs=pairs)
+    try:
+        _composite_parity_case(dev, orc, "cull_%g_%g" % (rmed, aniso), [1500], 105, 71, rmed, aniso)
+    finally:
+        B.set_tuning(**prev)
+
+
 def _composite_parity_case(dev, orc, name, counts, W, H, rmed, aniso):
     import torch
     from paper_2604_12626_amd import binding as B

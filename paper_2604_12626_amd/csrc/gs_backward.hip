@@ -585,28 +585,50 @@ __global__ void __launch_bounds__(1024) zero_and_list_kernel(const BackwardProje
 // colour (SH coefficients, and the view direction's share of the mean's
 // gradient, handed to wave 0 through LDS): two chains of half the length,
 // each holding about half the registers.
-template <int D>
-__global__ void __launch_bounds__(128) backward_project_kernel(const BackwardProjectArgs a) {
+// Bounded by the latency of the gathered accumulators and, with several views,
+// by memory traffic: what counts is the waves in flight (several views: three
+// per SIMD, so the rotation and the scales are computed again behind the views'
+// loop rather than held over it) and the rounds of dependent loads (one view,
+// ONE: no loop, and the accumulators requested with the parameters).  The SH
+// gradients leave through LDS, consecutive lanes on consecutive 16-byte pieces
+// of a row: stored by each lane for its own row they were 50 M of 64-byte write
+// requests for a million Gaussians at degree 3, and bound the kernel.  Measured
+// (the 16-view joint step, room of 1 M and 8 x 50 k avatar Gaussians; one view
+// of 1280x720; one of 256x256): 490 + 190, 16.0 and 10.7 us before, 321 + 118,
+// 13.6 and 7.6 us with all three.  SH rows read through LDS the same way cost
+// 33 us (a further round in the chain); four waves per SIMD, with spills, 60.
+template <int D, bool ONE>
+__global__ void __launch_bounds__(128, ONE ? 2 : 3) backward_project_kernel(const BackwardProjectArgs a) {
     constexpr int K = (D + 1) * (D + 1);
+    // SH gradients leave in pieces of 16 bytes (4-byte aligned) where a row is
+    // whole pieces, else of 4; the rows' stride in LDS keeps consecutive lanes
+    // on different banks
+    constexpr int kPiece = 3 * K % 4 == 0 ? 4 : 1, kPieces = 3 * K / kPiece;
+    constexpr int kRow = kPiece == 4 ? 4 * (kPieces | 1) : (3 * K) | 1;
+    typedef float Piece __attribute__((ext_vector_type(kPiece), aligned(4)));
     __shared__ float s_cam[kProjViews * kCamStride];
     __shared__ double s_dmu[3][64];
-    const uint32_t count = *a.count;
-    if ((int64_t)blockIdx.x * 64 >= (int64_t)count) return;  // uniform per workgroup
-    for (int k = threadIdx.x; k < a.nv * 16; k += 128) {
+    __shared__ float s_dsh[64 * kRow] __attribute__((aligned(16)));
+    __shared__ uint32_t s_id[64];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int nv = ONE ? 1 : a.nv;
+    // the count, the listed Gaussian and the cameras in one round of loads
+    const int64_t li = (int64_t)blockIdx.x * 64 + lane;
+    const uint32_t count = *a.count, listed = a.list[li < a.seg.n ? li : a.seg.n - 1];
+    for (int k = threadIdx.x; k < nv * 16; k += 128) {
         const int vi = k >> 4, f = k & 15;
         s_cam[vi * kCamStride + f] = reinterpret_cast<const float *>(a.cams + a.view[vi])[f];
     }
+    if ((int64_t)blockIdx.x * 64 >= (int64_t)count) return;  // uniform per workgroup
     __syncthreads();
-    for (int vi = threadIdx.x; vi < a.nv; vi += 128) {
+    for (int vi = threadIdx.x; vi < nv; vi += 128) {
         float *c = s_cam + vi * kCamStride;
 #pragma unroll
         for (int j = 0; j < 3; ++j) c[16 + j] = -(c[j] * c[9] + c[3 + j] * c[10] + c[6 + j] * c[11]);
     }
     __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t li = (int64_t)blockIdx.x * 64 + lane;
     const bool valid = li < (int64_t)count;
-    const int64_t i = valid ? (int64_t)a.list[li] : 0;
+    const int64_t i = valid ? (int64_t)listed : 0;
     const bool use_cov6 = a.seg.cov6 != nullptr;
     const gs_gaussians_grad &G = a.grad;
     const bool first = a.first != 0;
@@ -628,7 +650,7 @@ __global__ void __launch_bounds__(128) backward_project_kernel(const BackwardPro
         my = a.seg.means[3 * i + 1];
         mz = a.seg.means[3 * i + 2];
         drawn = 1u;
-        if (a.nv > 1) {
+        if (!ONE) {
             drawn = 0u;
             for (int v0 = 0; v0 < a.nv; v0 += 16) {
                 uint32_t t[16];
@@ -639,6 +661,7 @@ __global__ void __launch_bounds__(128) backward_project_kernel(const BackwardPro
             }
         }
     }
+    const double *g_one = a.g2d + (size_t)(a.base[0] + i) * kG2D;
     if (wave == 1) {
         // ---- colour -> SH coefficients and view direction
         float dsh[3 * K];
@@ -646,17 +669,24 @@ __global__ void __launch_bounds__(128) backward_project_kernel(const BackwardPro
         for (int k = 0; k < 3 * K; ++k) dsh[k] = 0.f;
         double dmd[3] = {0.0, 0.0, 0.0};
         float sh[3 * K];
-#pragma unroll
-        for (int k = 0; k < 3 * K; ++k) sh[k] = 0.f;
-        if (valid) {
-            const float *src = a.seg.sh + (size_t)(3 * K) * i;
-#pragma unroll
-            for (int k = 0; k < 3 * K; ++k) sh[k] = src[k];
+        float dc[3];
+        if (ONE && valid) {
+            dc[0] = (float)g_one[kGR];
+            dc[1] = (float)g_one[kGG];
+            dc[2] = (float)g_one[kGBl];
         }
-        for (uint64_t m = drawn; m; m &= m - 1u) {
-            const int vi = __ffsll((unsigned long long)m) - 1;
-            const double *g = a.g2d + (size_t)(a.base[vi] + i) * kG2D;
-            float dc[3] = {(float)g[kGR], (float)g[kGG], (float)g[kGBl]};
+        s_id[lane] = (uint32_t)i;
+        const float *src = a.seg.sh + (size_t)(3 * K) * i;
+#pragma unroll
+        for (int k = 0; k < 3 * K; ++k) sh[k] = src[k];
+        for (uint64_t m = drawn; m; m = ONE ? 0u : m & (m - 1u)) {
+            const int vi = ONE ? 0 : __ffsll((unsigned long long)m) - 1;
+            if (!ONE) {
+                const double *g = a.g2d + (size_t)(a.base[vi] + i) * kG2D;
+                dc[0] = (float)g[kGR];
+                dc[1] = (float)g[kGG];
+                dc[2] = (float)g[kGBl];
+            }
             const float *cam = s_cam + vi * kCamStride;
             float dx0 = mx - cam[16], dy0 = my - cam[17], dz0 = mz - cam[18];
             const float inv_dist = 1.0f / sqrtf(dx0 * dx0 + dy0 * dy0 + dz0 * dz0);
@@ -687,10 +717,22 @@ __global__ void __launch_bounds__(128) backward_project_kernel(const BackwardPro
             dmd[1] += (double)((ddy - y * dd) * inv_dist);
             dmd[2] += (double)((ddz - z * dd) * inv_dist);
         }
-        if (valid) {
-            float *dst = G.sh + (size_t)(3 * K) * i;
+        const int pieces = kPieces * (int)(count - blockIdx.x * 64u < 64u ? count - blockIdx.x * 64u : 64u);
 #pragma unroll
-            for (int k = 0; k < 3 * K; ++k) put(&dst[k], dsh[k]);
+        for (int k = 0; k < 3 * K; ++k) s_dsh[lane * kRow + k] = dsh[k];
+        lds_wave_sync();
+#pragma unroll
+        for (int q = 0; q < kPieces; ++q) {
+            const int e = q * 64 + lane;
+            if (e < pieces) {
+                const int r = e / kPieces, c = kPiece * (e % kPieces);
+                Piece v;
+#pragma unroll
+                for (int k = 0; k < kPiece; ++k) v[k] = s_dsh[r * kRow + c + k];
+                Piece *dst = reinterpret_cast<Piece *>(G.sh + (size_t)(3 * K) * s_id[r] + c);
+                if (!first) v += *dst;
+                *dst = v;
+            }
         }
 #pragma unroll
         for (int k = 0; k < 3; ++k) s_dmu[k][lane] = dmd[k];
@@ -701,6 +743,11 @@ __global__ void __launch_bounds__(128) backward_project_kernel(const BackwardPro
     double scd[3] = {0.0, 0.0, 0.0};
     RotT<double> rotd;
     if (wave == 0 && valid) {
+        double gl[kG2D];
+        if (ONE) {
+#pragma unroll
+            for (int k = 0; k < kG2D; ++k) gl[k] = g_one[k];
+        }
         float S[6];
         double Sd[6];
         if (use_cov6) {
@@ -723,12 +770,13 @@ __global__ void __launch_bounds__(128) backward_project_kernel(const BackwardPro
             rotd = quat_rot_t<double>((double)q.x, (double)q.y, (double)q.z, (double)q.w);
             cov_from_rot_scale(rotd.R, scd, Sd);
         }
-        for (uint64_t m = drawn; m; m &= m - 1u) {
-            const int vi = __ffsll((unsigned long long)m) - 1;
-            const double *g = a.g2d + (size_t)(a.base[vi] + i) * kG2D;
-            double gl[kG2D];
+        for (uint64_t m = drawn; m; m = ONE ? 0u : m & (m - 1u)) {
+            const int vi = ONE ? 0 : __ffsll((unsigned long long)m) - 1;
+            if (!ONE) {
+                const double *g = a.g2d + (size_t)(a.base[vi] + i) * kG2D;
 #pragma unroll
-            for (int k = 0; k < kG2D; ++k) gl[k] = g[k];
+                for (int k = 0; k < kG2D; ++k) gl[k] = g[k];
+            }
             const float *cam = s_cam + vi * kCamStride;
             ViewProj p;
             // the same FP32 projection as the forward; the instance is known to
@@ -842,6 +890,12 @@ __global__ void __launch_bounds__(128) backward_project_kernel(const BackwardPro
         // adjoint of every entry of the full symmetric Sigma
         const double full[9] = {dS[0], dS[1], dS[2], dS[1], dS[3], dS[4], dS[2], dS[4], dS[5]};
         double dls[3], dq[4];
+        if (!ONE) {  // not held over the loop of the views: the registers bound the waves in flight
+            const float4 q = reinterpret_cast<const float4 *>(a.seg.quats)[i];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) scd[k] = exp((double)a.seg.log_scales[3 * i + k]);
+            rotd = quat_rot_t<double>((double)q.x, (double)q.y, (double)q.z, (double)q.w);
+        }
         cov_backward(rotd, scd, full, dls, dq);
         if (G.log_scales) {
 #pragma unroll
@@ -889,6 +943,12 @@ hipError_t launch_clear_g2d(const uint32_t *tiles_touched, int64_t n_instances, 
                          counts, n_counts, ranges, n_items, seg_list, seg_cap);
 }
 
+template <int D>
+static hipError_t launch_backward_chain(const BackwardProjectArgs &a, unsigned grid, hipStream_t s) {
+    if (a.nv == 1) return launch_kernel(backward_project_kernel<D, true>, dim3(grid), dim3(128), s, a);
+    return launch_kernel(backward_project_kernel<D, false>, dim3(grid), dim3(128), s, a);
+}
+
 hipError_t launch_backward_project(const BackwardProjectArgs &a, hipStream_t s) {
     if (a.seg.n == 0) return hipSuccess;
     const int K = (a.seg.sh_degree + 1) * (a.seg.sh_degree + 1);
@@ -899,10 +959,10 @@ hipError_t launch_backward_project(const BackwardProjectArgs &a, hipStream_t s) 
     if (a.nv == 0) return hipSuccess;
     const unsigned grid = (unsigned)((a.seg.n + 63) / 64);  // 64 listed Gaussians per two-wave workgroup
     switch (a.seg.sh_degree) {
-        case 0: return launch_kernel(backward_project_kernel<0>, dim3(grid), dim3(128), s, a);
-        case 1: return launch_kernel(backward_project_kernel<1>, dim3(grid), dim3(128), s, a);
-        case 2: return launch_kernel(backward_project_kernel<2>, dim3(grid), dim3(128), s, a);
-        default: return launch_kernel(backward_project_kernel<3>, dim3(grid), dim3(128), s, a);
+        case 0: return launch_backward_chain<0>(a, grid, s);
+        case 1: return launch_backward_chain<1>(a, grid, s);
+        case 2: return launch_backward_chain<2>(a, grid, s);
+        default: return launch_backward_chain<3>(a, grid, s);
     }
 }
 

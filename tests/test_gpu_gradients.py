@@ -389,3 +389,55 @@ def test_backward_nonfinite_pixel_adjoint_stays_with_its_gaussians(dev, checkpoi
         err = np.abs(got[k][rest] - want[k][rest]).max() / np.abs(want[k]).max()
         say("  %s: %.2e of the block's largest" % (k, err))
         assert err <= 1e-6
+
+
+CHAIN_CASES = [(0, 2, False), (1, 3, True), (2, 5, False), (3, 17, False), (3, 66, True)]
+
+
+@pytest.mark.parametrize("degree,V,cov", CHAIN_CASES, ids=["sh%d_%dviews%s" % (d, v, "_cov6" if c else "")
+                                                           for d, v, c in CHAIN_CASES])
+def test_backward_of_views_is_the_sum_over_single_views(dev, degree, V, cov):
+    """The parameter chain of one view, of several and of more than one launch
+    takes (64), on a Gaussian count that fills no workgroup: the gradients of
+    a batch are the sums over its views, each rendered alone.  Sums over views
+    are kept in FP32 (a launch's results, and within it the colour's), so the
+    two differ by V + 2 roundings of the sum of magnitudes at most; 1e-7 of the
+    block's largest gradient covers the order of the FP64 atomics."""
+    import torch
+    from paper_2604_12626_amd import render
+    W, H = 59, 43
+    g = synth.gaussians_cube(331, np.random.default_rng(17 + V), sh_degree=degree)
+    if cov:
+        S = synth.perturb(g, np.random.default_rng(18))["log_scales"]
+        sc = np.exp(S.astype(np.float64))
+        w, x, y, z = (g["quats"].astype(np.float64) / np.linalg.norm(g["quats"], axis=1, keepdims=True)).T
+        R = np.stack([1 - 2 * (y * y + z * z), 2 * (x * y - w * z), 2 * (x * z + w * y), 2 * (x * y + w * z),
+                      1 - 2 * (x * x + z * z), 2 * (y * z - w * x), 2 * (x * z - w * y), 2 * (y * z + w * x),
+                      1 - 2 * (x * x + y * y)], -1).reshape(-1, 3, 3)
+        M = R * sc[:, None, :]
+        C = M @ M.transpose(0, 2, 1)
+        g = {k: v for k, v in g.items() if k not in ("log_scales", "quats")}
+        g["cov6"] = np.stack([C[:, 0, 0], C[:, 0, 1], C[:, 0, 2], C[:, 1, 1], C[:, 1, 2], C[:, 2, 2]], -1).astype(F32)
+    fields = COV_FIELDS if cov else SQ_FIELDS
+    cams = np.stack([synth.identity_camera(60.0 + v, 58.0 + 2 * v, W / 2 + v % 7, H / 2 - v % 5) for v in range(V)])
+    cams = torch.from_numpy(np.ascontiguousarray(cams, F32)).to(dev)
+    tg = to_dev(g, dev)
+    G = [torch.from_numpy(x).to(dev) for x in _random_adjoints(np.random.default_rng(19), V, H, W)]
+    r = render.Renderer(W, H, capacity=1 << 18, device=dev)
+    f = r.render([tg], cams, [[0]] * V, checkpoints=False)
+    got = _np(r.backward([tg], cams, [[0]] * V, f, *G)[0])
+    total = {k: np.zeros_like(got[k]) for k in fields}
+    mag = {k: np.zeros_like(got[k]) for k in fields}
+    for v in range(V):
+        f = r.render([tg], cams[v:v + 1], [[0]], checkpoints=False)
+        one = _np(r.backward([tg], cams[v:v + 1], [[0]], f, *[x[v:v + 1].contiguous() for x in G])[0])
+        for k in fields:
+            total[k] += one[k]
+            mag[k] += np.abs(one[k])
+    for k in fields:
+        top = np.abs(total[k]).max()
+        assert top > 0
+        bound = (V + 2) * 2.0 ** -24 * mag[k] + 1e-7 * top
+        worst = (np.abs(got[k] - total[k]) / bound).max()
+        say("  %s: %.3g of the bound" % (k, worst))
+        assert worst <= 1.0, k

@@ -550,10 +550,14 @@ gs_status gs_composite_noalloc(const gs_projected *proj, const uint32_t *vals, c
 }
 
 // ---------------------------------------------------------------------------
-// workspace: per-instance screen-space accumulators, then the compacted
-// Gaussian list of one projection launch, then its counters (one per launch)
-static size_t bwd_list_offset(int64_t n_instances) {
+// workspace: screen-space accumulators, then the table of their rows, then the
+// compacted Gaussian list of one projection launch, then its counters (one per
+// launch)
+static size_t bwd_slots_offset(int64_t n_instances) {
     return ((size_t)(n_instances > 0 ? n_instances : 1) * gs::kG2D * sizeof(double) + 255) & ~(size_t)255;
+}
+static size_t bwd_list_offset(int64_t n_instances) {
+    return bwd_slots_offset(n_instances) + gs::slot_groups(n_instances > 0 ? n_instances : 1) * sizeof(uint4);
 }
 static size_t bwd_count_offset(int64_t n_instances) {
     return bwd_list_offset(n_instances) +
@@ -603,6 +607,7 @@ gs_status gs_render_backward(const gs_gaussians *segs, int32_t n_segs, const gs_
     double *g2d = static_cast<double *>(ws);
     uint32_t *list = reinterpret_cast<uint32_t *>(static_cast<char *>(ws) + bwd_list_offset(proj->n_instances));
     uint32_t *counts = reinterpret_cast<uint32_t *>(static_cast<char *>(ws) + bwd_count_offset(proj->n_instances));
+    uint4 *slots = reinterpret_cast<uint4 *>(static_cast<char *>(ws) + bwd_slots_offset(proj->n_instances));
     hipError_t e;
     int launch_no = 0;
     gs::BackwardTileArgs b = {};
@@ -615,6 +620,7 @@ gs_status gs_render_backward(const gs_gaussians *segs, int32_t n_segs, const gs_
     b.d_depth = d_depth;
     b.d_alpha = d_alpha;
     b.g2d = g2d;
+    b.slots = slots;
     b.ckpt_slots = gs::ckpt_slots(ckpt_floats);
     b.ckpt = b.ckpt_slots ? ckpt : nullptr;
     // the work list lives behind the checkpoints (the backward's own part of the buffer)
@@ -627,10 +633,10 @@ gs_status gs_render_backward(const gs_gaussians *segs, int32_t n_segs, const gs_
     b.T = tiles_x(p) * tiles_y(p);
     b.n_items = (int64_t)b.T * n_views;
     if (b.seg_list && b.n_items >= (int64_t)1 << 26) b.seg_list = nullptr;  // item ids need 26 bits
-    // only the drawn instances' accumulators are used, so only those are
-    // cleared, together with the list counters; the same launch builds the
+    // only the drawn instances have accumulators, whose rows are laid out and
+    // cleared here, together with the list counters; the same launch builds the
     // tile pass's segment list
-    e = gs::launch_clear_g2d(proj->tiles_touched, proj->n_instances, g2d, counts, kBwdMaxLaunches, b.ranges,
+    e = gs::launch_clear_g2d(proj->tiles_touched, proj->n_instances, slots, g2d, counts, kBwdMaxLaunches, b.ranges,
                              b.n_items, b.seg_list, (uint64_t)(b.ckpt_slots * gs::kListPerSlot), sm);
     if (e != hipSuccess) return hip_fail(e, "gs_render_backward");
     b.alpha_max = p->alpha_max;
@@ -673,7 +679,7 @@ gs_status gs_render_backward(const gs_gaussians *segs, int32_t n_segs, const gs_
             a.seg = segs[s];
             a.grad = grads[s];
             a.cams = cams;
-            a.tiles_touched = proj->tiles_touched;
+            a.slots = slots;
             a.g2d = g2d;
             a.nv = (int)std::min(views.size() - c, (size_t)gs::kProjViews);
             for (int k = 0; k < a.nv; ++k) {

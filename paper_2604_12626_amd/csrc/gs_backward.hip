@@ -139,7 +139,7 @@ __global__ void __launch_bounds__(64, 4) backward_tile_kernel(const BackwardTile
     __shared__ float2 s_e2[64];
     __shared__ __attribute__((aligned(16))) uint32_t s_pos[64];
     __shared__ float s_mom[kMoments][64];  // moments of the survivors
-    __shared__ uint32_t s_id[64];          // and their instances
+    __shared__ uint32_t s_row[64];         // and their rows of the accumulators
     static_assert(sizeof(Stage) >= 64 * kG2D * sizeof(double), "the adjoints of a chunk fit over the staging");
     double *out = reinterpret_cast<double *>(&s_st);
     float4 *e0s = s_st.e0, *e1s = s_st.e1;
@@ -308,6 +308,7 @@ __global__ void __launch_bounds__(64, 4) backward_tile_kernel(const BackwardTile
         const int32_t lo = max(hi - 64, seg_a);
         const uint32_t id = g;
         const float cu = q0.x, cv = q0.y, cA = q1.x, cB = q1.y, cC = q1.z, co = q1.w;
+        uint4 grp = make_uint4(0u, 0u, 0u, 0u);
         const bool hit = lo + lane < hi && entry_reaches_box(cu, cv, cA, cB, cC, co, a.alpha_min, bx0, by0,
                                                              bx0 + 7.0f, by0 + 7.0f);
         const uint64_t bal = __ballot(hit);
@@ -319,7 +320,7 @@ __global__ void __launch_bounds__(64, 4) backward_tile_kernel(const BackwardTile
             e1s[pos] = make_float4(e.c, e.o, e.z, e.r);
             e2s[pos] = make_float2(e.g, e.bl);
             s_pos[pos] = (uint32_t)lane;
-            s_id[pos] = id;
+            grp = a.slots[id >> 6];  // (in flight while the chunk is walked)
         }
         if (hi - 64 > seg_a) {
             g = g_next;
@@ -421,10 +422,11 @@ __global__ void __launch_bounds__(64, 4) backward_tile_kernel(const BackwardTile
 #pragma unroll
             for (int j = 0; j < kG2D; ++j) o[j] = 0.0;
         }
+        if (hit) s_row[__popcll(bal & gt_mask)] = slot_of(grp, id);
         lds_wave_sync();
         for (int i = lane; i < n * kG2D; i += 64) {
             const double v = out[i];
-            if (v != 0.0) atomicAdd(a.g2d + (size_t)s_id[i / kG2D] * kG2D + (i % kG2D), v);
+            if (v != 0.0) atomicAdd(a.g2d + (size_t)s_row[i / kG2D] * kG2D + (i % kG2D), v);
         }
         lds_wave_sync();
     }
@@ -532,21 +534,56 @@ __device__ __forceinline__ void zero_plane(float *p, int w, int64_t i0, int64_t 
 // workgroup from ballots and one atomic per workgroup (order of arrival: each
 // Gaussian is handled on its own).  A workgroup takes kListSpan Gaussians, so
 // that few atomics meet on the one counter (they serialise there).
+__device__ __forceinline__ bool drawn_in(const BackwardProjectArgs &a, int vi, int64_t i) {
+    const uint64_t inst = (uint64_t)(a.base[vi] + i);
+    return reinterpret_cast<const uint32_t *>(a.slots + (inst >> 6))[(inst >> 5) & 1u] >> (inst & 31u) & 1u;
+}
+__device__ __forceinline__ const double *row_of(const BackwardProjectArgs &a, int vi, int64_t i) {
+    const uint64_t inst = (uint64_t)(a.base[vi] + i);
+    return a.g2d + (size_t)slot_of(a.slots[inst >> 6], (uint32_t)inst) * kG2D;
+}
 constexpr int kListChunks = 4, kListSpan = 1024 * kListChunks;
 __global__ void __launch_bounds__(1024) zero_and_list_kernel(const BackwardProjectArgs a, int sh_floats) {
     __shared__ uint32_t s_cnt[kListChunks][16], s_base;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t g0 = (int64_t)blockIdx.x * kListSpan, g1 = g0 + kListSpan < a.seg.n ? g0 + kListSpan : a.seg.n;
-    bool vis[kListChunks];
+    // bal[c]: the drawn ones of the wave's 64 Gaussians of chunk c.  Lane v
+    // takes view v's (a launch has at most 64): its table words from the first
+    // of the 64 on, all loads in one round; a Gaussian is listed if any has it.
+    // (As a loop over the views in each lane, 33 + 16 us of a 16-view step; so,
+    // 10 + 7 us.)
     uint64_t bal[kListChunks];
+    {
+        uint2 w0[kListChunks], w1[kListChunks];
+        const uint64_t base = (uint64_t)a.base[lane < a.nv ? lane : 0];
 #pragma unroll
-    for (int c = 0; c < kListChunks; ++c) {
-        const int64_t i = g0 + c * 1024 + threadIdx.x;
-        vis[c] = false;
-        if (i < g1)
-            for (int vi = 0; vi < a.nv && !vis[c]; ++vi) vis[c] = a.tiles_touched[a.base[vi] + i] != 0u;
-        bal[c] = __ballot(vis[c]);
-        if (lane == 0) s_cnt[c][wave] = (uint32_t)__popcll(bal[c]);
+        for (int c = 0; c < kListChunks; ++c) {
+            const uint64_t i0 = (uint64_t)g0 + c * 1024 + 64 * wave, inst = base + i0;
+            w0[c] = w1[c] = make_uint2(0u, 0u);
+            if (lane < a.nv && i0 < (uint64_t)g1) w0[c] = *reinterpret_cast<const uint2 *>(a.slots + (inst >> 6));
+            if (lane < a.nv && (inst >> 6) * 64 + 64 < base + (uint64_t)g1)
+                w1[c] = *reinterpret_cast<const uint2 *>(a.slots + (inst >> 6) + 1);
+        }
+#pragma unroll
+        for (int c = 0; c < kListChunks; ++c) {
+            const int64_t i0 = g0 + c * 1024 + 64 * wave;
+            const uint32_t sh = (uint32_t)(base + (uint64_t)i0) & 63u;
+            const uint64_t lo = (uint64_t)w0[c].y << 32 | w0[c].x, hi = (uint64_t)w1[c].y << 32 | w1[c].x;
+            uint64_t m = lo >> sh | (sh ? hi << (64u - sh) : 0ull);
+            uint32_t x = (uint32_t)m, y = (uint32_t)(m >> 32);
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1)
+                if (off < a.nv) {
+                    x |= (uint32_t)__shfl_xor((int)x, off, 64);
+                    y |= (uint32_t)__shfl_xor((int)y, off, 64);
+                }
+            x = (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+            y = (uint32_t)__builtin_amdgcn_readfirstlane((int)y);
+            m = (uint64_t)y << 32 | x;
+            const int64_t left = g1 - i0;  // (the words go on with other segments' instances)
+            bal[c] = left <= 0 ? 0ull : left < 64 ? m & ((1ull << left) - 1ull) : m;
+            if (lane == 0) s_cnt[c][wave] = (uint32_t)__popcll(bal[c]);
+        }
     }
     if (a.first && !a.zeroed) {
         const gs_gaussians_grad &G = a.grad;
@@ -574,7 +611,7 @@ __global__ void __launch_bounds__(1024) zero_and_list_kernel(const BackwardProje
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < kListChunks; ++c)
-        if (vis[c])
+        if (bal[c] >> lane & 1ull)
             a.list[s_base + s_cnt[c][wave] + (uint32_t)__popcll(bal[c] & ((1ull << lane) - 1ull))] =
                 (uint32_t)(g0 + c * 1024 + threadIdx.x);
 }
@@ -653,15 +690,18 @@ __global__ void __launch_bounds__(128, ONE ? 2 : 3) backward_project_kernel(cons
         if (!ONE) {
             drawn = 0u;
             for (int v0 = 0; v0 < a.nv; v0 += 16) {
-                uint32_t t[16];
+                bool t[16];
 #pragma unroll
-                for (int k = 0; k < 16; ++k) t[k] = v0 + k < a.nv ? a.tiles_touched[a.base[v0 + k] + i] : 0u;
+                for (int k = 0; k < 16; ++k) t[k] = v0 + k < a.nv && drawn_in(a, v0 + k, i);
 #pragma unroll
-                for (int k = 0; k < 16; ++k) drawn |= (uint64_t)(t[k] != 0u) << (v0 + k);
+                for (int k = 0; k < 16; ++k) drawn |= (uint64_t)t[k] << (v0 + k);
             }
         }
     }
-    const double *g_one = a.g2d + (size_t)(a.base[0] + i) * kG2D;
+    // the row of the first view that draws it; inside the loops the next one's
+    // is looked up while one is worked on
+    auto next_row = [&](uint64_t m) { return row_of(a, m ? __ffsll((unsigned long long)m) - 1 : 0, i); };
+    const double *g = next_row(drawn);
     if (wave == 1) {
         // ---- colour -> SH coefficients and view direction
         float dsh[3 * K];
@@ -671,9 +711,9 @@ __global__ void __launch_bounds__(128, ONE ? 2 : 3) backward_project_kernel(cons
         float sh[3 * K];
         float dc[3];
         if (ONE && valid) {
-            dc[0] = (float)g_one[kGR];
-            dc[1] = (float)g_one[kGG];
-            dc[2] = (float)g_one[kGBl];
+            dc[0] = (float)g[kGR];
+            dc[1] = (float)g[kGG];
+            dc[2] = (float)g[kGBl];
         }
         s_id[lane] = (uint32_t)i;
         const float *src = a.seg.sh + (size_t)(3 * K) * i;
@@ -682,10 +722,10 @@ __global__ void __launch_bounds__(128, ONE ? 2 : 3) backward_project_kernel(cons
         for (uint64_t m = drawn; m; m = ONE ? 0u : m & (m - 1u)) {
             const int vi = ONE ? 0 : __ffsll((unsigned long long)m) - 1;
             if (!ONE) {
-                const double *g = a.g2d + (size_t)(a.base[vi] + i) * kG2D;
                 dc[0] = (float)g[kGR];
                 dc[1] = (float)g[kGG];
                 dc[2] = (float)g[kGBl];
+                g = next_row(m & (m - 1u));
             }
             const float *cam = s_cam + vi * kCamStride;
             float dx0 = mx - cam[16], dy0 = my - cam[17], dz0 = mz - cam[18];
@@ -746,7 +786,7 @@ __global__ void __launch_bounds__(128, ONE ? 2 : 3) backward_project_kernel(cons
         double gl[kG2D];
         if (ONE) {
 #pragma unroll
-            for (int k = 0; k < kG2D; ++k) gl[k] = g_one[k];
+            for (int k = 0; k < kG2D; ++k) gl[k] = g[k];
         }
         float S[6];
         double Sd[6];
@@ -773,9 +813,9 @@ __global__ void __launch_bounds__(128, ONE ? 2 : 3) backward_project_kernel(cons
         for (uint64_t m = drawn; m; m = ONE ? 0u : m & (m - 1u)) {
             const int vi = ONE ? 0 : __ffsll((unsigned long long)m) - 1;
             if (!ONE) {
-                const double *g = a.g2d + (size_t)(a.base[vi] + i) * kG2D;
 #pragma unroll
                 for (int k = 0; k < kG2D; ++k) gl[k] = g[k];
+                g = next_row(m & (m - 1u));
             }
             const float *cam = s_cam + vi * kCamStride;
             ViewProj p;
@@ -908,38 +948,60 @@ __global__ void __launch_bounds__(128, ONE ? 2 : 3) backward_project_kernel(cons
     }
 }
 
-// The screen-space accumulators of the drawn instances start at zero; B1
-// adds only to those and B2 reads only those.  Workgroup 0 also zeroes the
-// list counters and, with checkpoints and at most kListInClear lists, builds
-// the tile pass's segment list.
-__global__ void __launch_bounds__(256) clear_g2d_kernel(const uint32_t *tt, int64_t n, double *g2d,
+// The rows of the drawn instances (slot_of), cleared: B1 adds only to those and
+// B2 reads only those.  Rows close together: at the instance's own place, a
+// fifth of 22 M instances drawn, 208 us; so, 93 us, and B2's gathers 321 + 118
+// -> 300 + 112 us.  Workgroup 0 also zeroes the list counters and, with
+// checkpoints and at most kListInClear lists, builds the tile pass's segment
+// list.
+__global__ void __launch_bounds__(256) clear_g2d_kernel(const uint32_t *tt, int64_t n, uint4 *slots, double *g2d,
                                                         uint32_t *counts, int n_counts, const uint2 *ranges,
                                                         int64_t n_items, uint32_t *seg_list, uint64_t seg_cap) {
     static_assert(kG2D % 2 == 0, "two accumulators per 16-B store");
-    constexpr uint32_t P = kG2D / 2;  // 16-B pieces per instance
+    static_assert(kSlotChunk == 1024, "four groups of 64 instances for each of four waves");
+    __shared__ uint32_t s_w[4];
     if (blockIdx.x == 0) {
         for (int k = threadIdx.x; k < n_counts; k += 256) counts[k] = 0u;
         if (seg_list && n_items <= kListInClear) build_segment_list<256>(ranges, n_items, seg_list, seg_cap);
     }
-    // a block of 256 instances at a time, its 256 P pieces spread over the
-    // threads, so that each store instruction writes consecutive 16-B pieces
-    for (int64_t base = (int64_t)blockIdx.x * 256; base < n; base += (int64_t)gridDim.x * 256) {
-        double2 *g = reinterpret_cast<double2 *>(g2d + (size_t)base * kG2D);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int64_t c0 = (int64_t)blockIdx.x * kSlotChunk; c0 < n; c0 += (int64_t)gridDim.x * kSlotChunk) {
+        uint64_t drawn[4];
+        uint32_t mine = 0u;
 #pragma unroll
-        for (uint32_t r = 0; r < P; ++r) {
-            const uint32_t k = r * 256u + threadIdx.x, li = k / P;
-            if (base + li < n && tt[base + li]) g[k] = make_double2(0.0, 0.0);
+        for (int k = 0; k < 4; ++k) {
+            const int64_t i = c0 + 256 * wave + 64 * k + lane;
+            drawn[k] = __ballot(i < n && tt[i] != 0u);
+            mine += (uint32_t)__popcll(drawn[k]);
         }
+        if (lane == 0) s_w[wave] = mine;
+        __syncthreads();
+        uint32_t row = 0u, total = 0u;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            row += w < wave ? s_w[w] : 0u;
+            total += s_w[w];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (lane == k)
+                slots[c0 / 64 + 4 * wave + k] = make_uint4((uint32_t)drawn[k], (uint32_t)(drawn[k] >> 32),
+                                                           (uint32_t)c0 + row, 0u);
+            row += (uint32_t)__popcll(drawn[k]);
+        }
+        double2 *g = reinterpret_cast<double2 *>(g2d + (size_t)c0 * kG2D);
+        for (uint32_t k = threadIdx.x; k < total * (kG2D / 2); k += 256) g[k] = make_double2(0.0, 0.0);
     }
 }
 
-hipError_t launch_clear_g2d(const uint32_t *tiles_touched, int64_t n_instances, double *g2d, uint32_t *counts,
-                            int n_counts, const uint2 *ranges, int64_t n_items, uint32_t *seg_list, uint64_t seg_cap,
-                            hipStream_t s) {
-    int64_t grid = (n_instances + 255) / 256;
-    if (grid > 8192) grid = 8192;
+hipError_t launch_clear_g2d(const uint32_t *tiles_touched, int64_t n_instances, uint4 *slots, double *g2d,
+                            uint32_t *counts, int n_counts, const uint2 *ranges, int64_t n_items, uint32_t *seg_list,
+                            uint64_t seg_cap, hipStream_t s) {
+    int64_t grid = (n_instances + kSlotChunk - 1) / kSlotChunk;
+    if (grid > 1 << 20) grid = 1 << 20;
     if (grid < 1) grid = 1;
-    return launch_kernel(clear_g2d_kernel, dim3((unsigned)grid), dim3(256), s, tiles_touched, n_instances, g2d,
+    return launch_kernel(clear_g2d_kernel, dim3((unsigned)grid), dim3(256), s, tiles_touched, n_instances, slots, g2d,
                          counts, n_counts, ranges, n_items, seg_list, seg_cap);
 }
 

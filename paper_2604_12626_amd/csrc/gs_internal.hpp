@@ -44,12 +44,28 @@ struct ProjectArgs {
     float near_plane, lowpass, sigma_cut, fov_clamp;
 };
 
+// Screen-space accumulators: one row per drawn instance, the rows of a chunk of
+// kSlotChunk instances together at the chunk's start, in instance order (of
+// the instances of 16 views a fifth is drawn, and scattered rows of 80 bytes
+// write and fetch the lines between them).  Per 64 instances: which of them are
+// drawn (x, y) and the row of the first of those (z).
+constexpr int kSlotChunk = 1024;
+inline size_t slot_groups(int64_t n_instances) {
+    return (size_t)((n_instances + kSlotChunk - 1) / kSlotChunk) * (kSlotChunk / 64);
+}
+__device__ __forceinline__ uint32_t slot_of(const uint4 group, uint32_t instance) {
+    const uint32_t b = instance & 63u;
+    const uint32_t lo = b < 32u ? group.x & ((1u << b) - 1u) : group.x;
+    const uint32_t hi = b < 32u ? 0u : group.y & ((1u << (b - 32u)) - 1u);
+    return group.z + __popc(lo) + __popc(hi);
+}
+
 struct BackwardProjectArgs {
     gs_gaussians seg;
     gs_gaussians_grad grad;
     const gs_camera *cams;
-    const uint32_t *tiles_touched;
-    const double *g2d;  // [instances][kG2D]
+    const uint4 *slots;  // which instances are drawn, and their rows of g2d (slot_of)
+    const double *g2d;   // [rows][kG2D]
     int64_t base[kProjViews];
     int32_t view[kProjViews];
     int32_t nv;
@@ -112,7 +128,8 @@ struct BackwardTileArgs {
     const float *t_final;
     const uint32_t *n_contrib;
     const float *d_rgb, *d_depth, *d_alpha;
-    double *g2d;  // [instances][kG2D], FP64 accumulators
+    const uint4 *slots;  // instance -> row of g2d (slot_of)
+    double *g2d;         // [rows][kG2D], FP64 accumulators
     const float *ckpt;   // segment checkpoints, or null (one walk per list)
     uint64_t ckpt_slots;
     uint32_t *seg_list;  // (item << 6 | segment) of every segment to walk, after a count
@@ -223,7 +240,7 @@ hipError_t launch_backward_tiles(BackwardTileArgs a, int n_cu, hipStream_t s);
 hipError_t launch_backward_project(const BackwardProjectArgs &a, hipStream_t s);
 // zeroes the screen-space accumulators of the drawn instances (tiles_touched
 // > 0) and the n_counts list counters
-hipError_t launch_clear_g2d(const uint32_t *tiles_touched, int64_t n_instances, double *g2d, uint32_t *counts,
+hipError_t launch_clear_g2d(const uint32_t *tiles_touched, int64_t n_instances, uint4 *slots, double *g2d, uint32_t *counts,
                             int n_counts, const uint2 *ranges, int64_t n_items, uint32_t *seg_list, uint64_t seg_cap,
                             hipStream_t s);  // seg_list: the tile pass's work list, built too when non-NULL
 hipError_t launch_lbs(const LbsArgs &a, bool backward, hipStream_t s);

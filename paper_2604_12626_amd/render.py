@@ -61,6 +61,8 @@ class Renderer:
         self.device = torch.device(device)
         self.capacity = int(capacity)
         self._bufs = {}
+        self._shaped = None  # (sizes, a frame's shaped views of the buffers)
+        self._flag = self._flag_ready = None  # the overflow flag on the host (pinned), and its copy's event
 
     # -- buffers ------------------------------------------------------------
     def _buf(self, name, shape, dtype, zero=False):
@@ -74,6 +76,19 @@ class Renderer:
         return t[:n].view(*shape) if len(shape) else t[:1]
 
     def alloc_frame(self, n_inst, n_views, ckpt=False):
+        """A Frame over the renderer's buffers, each tensor a new alias.  The
+        shaped views of the last sizes are kept: cutting them anew took most
+        of a small frame's host time."""
+        sizes = (n_inst, n_views, ckpt, self.capacity)
+        if self._shaped is None or self._shaped[0] != sizes:
+            self._shaped = (sizes, vars(self._shape_frame(n_inst, n_views, ckpt)))
+        f = Frame()
+        for name, t in self._shaped[1].items():
+            if t is not None:
+                setattr(f, name, t.detach())
+        return f
+
+    def _shape_frame(self, n_inst, n_views, ckpt):
         f = Frame()
         f.tiles_touched = self._buf("tt", (n_inst,), torch.int32)
         f.rec = self._buf("rec", (n_inst, B.REC_FLOATS), torch.float32)
@@ -115,6 +130,30 @@ class Renderer:
         self.bin_sort(f, n_views)
         self.composite(f, n_views)
 
+    def _forward(self, segs, cams, view_segs, f, check, ahead):
+        """All forward stages; with `check`, waits for the binning and returns
+        whether it overflowed.  `ahead`: the flag is copied to the host between
+        the binning and the compositing, so that the GPU goes on while the host
+        waits for it (after an overflow every tile list is empty and the images
+        are the background: harmless, and drawn again); else the compositing is
+        left out after an overflow."""
+        n_views = len(view_segs)
+        self.project(segs, cams, view_segs, f)
+        self.bin_sort(f, n_views)
+        if check and not ahead and int(f.overflow.item()):
+            return True
+        if check and ahead:
+            if self._flag is None:
+                self._flag = torch.empty(1, dtype=torch.int32, pin_memory=True)
+                self._flag_ready = torch.cuda.Event()
+            self._flag.copy_(f.overflow, non_blocking=True)
+            self._flag_ready.record(torch.cuda.current_stream(self.device))
+        self.composite(f, n_views)
+        if check and ahead:
+            self._flag_ready.synchronize()
+            return bool(int(self._flag))
+        return False
+
     def render(self, segs, cams, view_segs=None, sync_check=True, checkpoints=None):
         """Eager forward.  Returns a Frame whose tensors are views of the
         renderer's buffers (valid until the next call).  checkpoints (default:
@@ -126,17 +165,14 @@ class Renderer:
         n_views = len(view_segs)
         ckpt = (n_views * self.T <= self.AUTO_CHECKPOINT_ITEMS) if mode == "auto" else bool(mode)
         n_inst = B.instance_offsets(segs, view_segs)[-1]
+        # the capacity has held a frame of these sizes: expect it to hold this one
+        ahead = self._shaped is not None and self._shaped[0] == (n_inst, n_views, ckpt, self.capacity)
         f = self.alloc_frame(n_inst, n_views, ckpt)
-        self.project(segs, cams, view_segs, f)
-        self.bin_sort(f, n_views)
-        if sync_check and int(f.overflow.item()):
+        if self._forward(segs, cams, view_segs, f, sync_check, ahead):
             self.capacity = min(_grow(int(f.num.item())), B.MAX_CAPACITY)
             f = self.alloc_frame(n_inst, n_views, ckpt)
-            self.project(segs, cams, view_segs, f)
-            self.bin_sort(f, n_views)
-            if int(f.overflow.item()):
+            if self._forward(segs, cams, view_segs, f, sync_check, False):
                 raise RuntimeError("tile instances %d exceed the maximum capacity" % int(f.num.item()))
-        self.composite(f, n_views)
         f.n_views = n_views
         f.n_inst = n_inst
         return f

@@ -450,6 +450,36 @@ def test_render_deterministic_and_batched_equals_plain(dev):
         assert torch.equal(f1.alpha[0], a1[2][k])
 
 
+def test_render_overflow_at_known_sizes(dev):
+    """A renderer whose capacity held a frame of some sizes composites the next
+    frame of those sizes before it knows whether the keys fit.  When they do
+    not, the frame is the one of a large capacity, and it fits from then on;
+    each frame's tensors are objects of their own."""
+    import torch
+    from paper_2604_12626_amd import render
+    W, H = 160, 96
+    g = to_dev(synth.gaussians_cube(20_000, np.random.default_rng(5), sh_degree=1), dev)
+    few = synth.identity_camera(120.0, 120.0, W + 20.0, H / 2)  # most of the cube right of the image
+    many = synth.identity_camera(120.0, 120.0, W / 2, H / 2)
+    few, many = (torch.from_numpy(c[None].astype(F32)).to(dev) for c in (few, many))
+    want = {}
+    for name, cam in (("few", few), ("many", many)):
+        f = render.Renderer(W, H, capacity=1 << 22, device=dev).render([g], cam, [[0]])
+        want[name] = (int(f.num.item()), f.rgb.clone(), f.depth.clone(), f.n_contrib.clone())
+    cap = (want["few"][0] + want["many"][0]) // 2
+    assert want["few"][0] < cap < want["many"][0]
+    r = render.Renderer(W, H, capacity=cap, device=dev)
+    last = None
+    for name, cam in (("few", few), ("few", few), ("many", many), ("many", many), ("few", few)):
+        f = r.render([g], cam, [[0]])
+        assert int(f.overflow.item()) == 0 and int(f.num.item()) == want[name][0]
+        for got, ref in zip((f.rgb, f.depth, f.n_contrib), want[name][1:]):
+            assert torch.equal(got, ref), name
+        assert last is None or (f.rgb is not last.rgb and f.rec is not last.rec)
+        last = f
+    assert r.capacity > want["many"][0]
+
+
 def test_composite_schedule_does_not_change_results(dev):
     """Every launch configuration the autotuner may pick (persistent groups
     per CU) gives bit-identical images; the tuner leaves one of them set."""

@@ -217,7 +217,7 @@ struct SortPlan {
     int64_t scan_blocks, sort_parts;
     // workspace layout (byte offsets)
     size_t off_part, off_keys2, off_vals2, off_rows, off_dbase, off_tcnt, off_tcount, off_tover, off_tstart, off_comp,
-        off_compn, off_slist, off_sctl, off_rlist, off_hist, off_status, off_ticket, total;
+        off_compn, off_slist, off_sctl, off_rlist, off_tstat, off_hist, off_status, off_ticket, total;
 };
 
 // launchers (one per translation unit)

@@ -951,7 +951,7 @@ constexpr int kLargeSortBlock = 1024, kLargeSortCap = 8192;
 constexpr int kTileSortBlock = 1024, kTileSortCap = 16384;
 constexpr int kSortClasses = 5;
 
-// Exclusive scan of the tile totals (one workgroup): the key count and the
+// Exclusive scan of the tile totals: the key count and the
 // overflow flag (count above the capacity), each tile's first key, the
 // ranges ([first, end) for tiles with keys, [0, 0) otherwise, and all [0, 0)
 // after an overflow), the compositing work order, and the lists the tile
@@ -959,9 +959,7 @@ constexpr int kSortClasses = 5;
 // kLargeSortCap keys by descending length (in bins of 1024 keys), then those
 // of the four shorter classes, longest class first; sort_ctl holds the five
 // counts, the number of tiles of more than kTileSortCap keys and of their runs
-// of up to kTileSortCap keys, which run_list holds as {tile, run}.  Counts are read coalesced, a chunk of
-// up to kScanChunk tiles at a time, into LDS.
-constexpr int kScanChunk = 16384;
+// of up to kTileSortCap keys, which run_list holds as {tile, run}.
 constexpr int kSortBins = 64;
 constexpr int kHugeBins = kSortBins - kTileSortCap / 1024;  // the bins of the tiles longer than kTileSortCap
 // sort_ctl: the five class counts, then the number of tiles longer than
@@ -979,215 +977,299 @@ __device__ __forceinline__ uint32_t sort_bin(uint32_t len) {
     return (uint32_t)(kSortBins - 1) - (k < (uint32_t)(kSortBins - 1) ? k : (uint32_t)(kSortBins - 1));
 }
 
-// One slot per active lane from *counter (lanes in order): one LDS atomic
-// for the wave.
-__device__ __forceinline__ uint32_t wave_append(uint32_t *counter, bool active) {
-    const int lane = threadIdx.x & 63;
-    const uint64_t m = __ballot(active);
-    if (!m) return 0u;  // uniform
-    const int leader = __ffsll((unsigned long long)m) - 1;
-    uint32_t b = 0u;
-    if (lane == leader) b = atomicAdd(counter, (uint32_t)__popcll(m));
-    b = __builtin_amdgcn_readlane(b, leader);
-    return b + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+struct TileScanArgs {
+    const uint32_t *tile_count;  // keys per tile
+    const uint32_t *tile_over;   // and, windowed, those counted outside a window
+    int n_tiles;
+    int64_t capacity;
+    uint32_t *tile_start, *ranges, *order, *sort_list, *sort_ctl;
+    uint2 *run_list;
+    uint32_t *stats;  // [workgroups][kStatWords] (tile_stats_kernel)
+    int64_t *d_num;
+    int32_t *d_overflow;
+};
+
+__device__ __forceinline__ uint32_t tile_runs(uint32_t len) {
+    return len > (uint32_t)kTileSortCap ? (len + kTileSortCap - 1) / kTileSortCap : 0u;
 }
 
+// counts `len` (0: not listed) in the list bins: long tiles by one atomic each,
+// the shorter classes by one for the wave, lanes 0 .. 3 a class each
+__device__ __forceinline__ void count_sort_bin(uint32_t *s_big, uint32_t len) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t bin = sort_bin(len);
+    if (len && bin < (uint32_t)kSortBins) atomicAdd(&s_big[bin], 1u);
+    uint32_t mine = 0u;
+#pragma unroll
+    for (int cl = 0; cl < kSortClasses - 1; ++cl) {
+        const uint64_t m = __ballot(len && bin == (uint32_t)(kSortBins + cl));
+        if (lane == cl) mine = (uint32_t)__popcll(m);
+    }
+    if (mine) atomicAdd(&s_big[kSortBins + lane], mine);
+}
+
+// the tile's place in the sort list (s_big: the next place of every bin), and
+// its runs' in the run list
+__device__ __forceinline__ void list_tile(const TileScanArgs &A, uint32_t *s_big, uint32_t *s_runs, uint32_t t,
+                                          uint32_t len) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t bin = sort_bin(len);
+    uint32_t slot = 0u, mine = 0u;
+#pragma unroll
+    for (int cl = 0; cl < kSortClasses - 1; ++cl) {
+        const bool in_cl = len && bin == (uint32_t)(kSortBins + cl);
+        const uint64_t m = __ballot(in_cl);
+        if (lane == cl) mine = (uint32_t)__popcll(m);
+        if (in_cl) slot = (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+    }
+    if (lane < kSortClasses - 1 && mine) mine = atomicAdd(&s_big[kSortBins + lane], mine);
+    slot += __shfl(mine, (int)(bin - (uint32_t)kSortBins) & 3, 64);
+    if (len) A.sort_list[bin < (uint32_t)kSortBins ? atomicAdd(&s_big[bin], 1u) : slot] = t;
+    const uint32_t R = tile_runs(len);
+    if (R) {
+        const uint32_t r0 = atomicAdd(s_runs, R);
+        for (uint32_t r = 0; r < R; ++r) A.run_list[r0 + r] = make_uint2(t, r);
+    }
+}
+
+// by one wave: the list bins' counts all[b] -> the first place of every bin, plus
+// before[b]; the counts to sort_ctl where `ctl` is set
+__device__ __forceinline__ void sort_bin_starts(const uint32_t *all, const uint32_t *before, uint32_t *starts,
+                                                uint32_t *ctl) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t b = all[lane];
+    uint32_t incl = b;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += y;
+    }
+    const uint32_t n_huge = __shfl(incl - b, kHugeBins, 64), n_long = __shfl(incl, 63, 64);
+    uint32_t cls[kSortClasses - 1];
+#pragma unroll
+    for (int cl = 0; cl < kSortClasses - 1; ++cl) cls[cl] = all[kSortBins + cl];
+    starts[lane] = incl - b + (before ? before[lane] : 0u);
+    if (lane == 0) {
+        // the shorter classes follow the long tiles, in order
+        uint32_t at = n_long;
+        if (ctl) {
+            ctl[0] = n_long;
+            ctl[kSortClasses] = n_huge;
+        }
+#pragma unroll
+        for (int cl = 0; cl < kSortClasses - 1; ++cl) {
+            if (ctl) ctl[1 + cl] = cls[cl];
+            starts[kSortBins + cl] = at + (before ? before[kSortBins + cl] : 0u);
+            at += cls[cl];
+        }
+    }
+}
+
+// inclusive scan of v over the workgroup's 1024 threads (s_w: 16 words)
+__device__ __forceinline__ uint64_t block1024_inclusive_scan(uint64_t v, uint64_t *s_w, uint64_t &total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint64_t y = __shfl_up(v, off, 64);
+        if (lane >= off) v += y;
+    }
+    if (lane == 63) s_w[wave] = v;
+    __syncthreads();
+    total = 0u;
+    for (int k = 0; k < 16; ++k) {
+        if (k < wave) v += s_w[k];
+        total += s_w[k];
+    }
+    return v;
+}
+
+// up to kScanTiles tiles, by one workgroup: PER * 1024 >= n_tiles (without 64-bit
+// indexes and with one LDS atomic a wave for the shorter classes, 1200 tiles take
+// 5.7 us, before 6.8)
+constexpr int kScanTiles = 4096;
 template <int PER>
-__global__ void __launch_bounds__(1024) bucket_tilescan_kernel(const uint32_t *tile_count, const uint32_t *tile_over,
-                                                               int64_t n_tiles, int64_t capacity, uint32_t *tile_start,
-                                                               uint32_t *ranges, uint32_t *order, uint32_t *sort_list,
-                                                               uint32_t *sort_ctl, uint2 *run_list, int64_t *d_num,
-                                                               int32_t *d_overflow) {
-    constexpr int CH = PER * 1024;  // tiles per chunk
-    __shared__ uint32_t s_runs;
-    __shared__ uint32_t s_c[CH];
-    __shared__ uint32_t s_st[CH];  // first keys of the chunk's tiles
+__global__ void __launch_bounds__(1024) bucket_tilescan_kernel(const TileScanArgs A) {
+    __shared__ uint32_t s_c[PER * 1024], s_st[PER * 1024];
     __shared__ uint64_t s_w[16];
     __shared__ uint32_t s_cnt[kOrderQueues][kOrderBins];
-    __shared__ uint32_t s_big[kSortBins + kSortClasses - 1];  // long tiles by bin, then the shorter classes
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t n_chunks = (n_tiles + CH - 1) / CH;
-    // keys per tile: the counted ones, plus those counted outside a window;
-    // s_c[k] = count of tile cb + k (0 past the end), loads in flight together
-    int64_t loaded = -1;
-    auto load_chunk = [&](int64_t cb) {
-        if (loaded == cb) return;  // uniform
-        __syncthreads();
+    __shared__ uint32_t s_big[kSortBins + kSortClasses - 1], s_runs;
+    const int tid = threadIdx.x, n_tiles = A.n_tiles;
+    {
         // every load issued before any is used: addresses clamped in bounds,
         // counts past the end zeroed afterwards
         uint32_t c[PER], o[PER];
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-            const int64_t t = min(cb + k * 1024 + tid, n_tiles - 1);
-            c[k] = tile_count[t];
-            o[k] = tile_over ? tile_over[t] : 0u;
+            const int t = min(k * 1024 + tid, n_tiles - 1);
+            c[k] = A.tile_count[t];
+            o[k] = A.tile_over ? A.tile_over[t] : 0u;
         }
 #pragma unroll
-        for (int k = 0; k < PER; ++k) s_c[k * 1024 + tid] = cb + k * 1024 + tid < n_tiles ? c[k] + o[k] : 0u;
-        loaded = cb;
-        __syncthreads();
-    };
+        for (int k = 0; k < PER; ++k) s_c[k * 1024 + tid] = k * 1024 + tid < n_tiles ? c[k] + o[k] : 0u;
+    }
     for (int i = tid; i < kOrderQueues * kOrderBins; i += 1024) (&s_cnt[0][0])[i] = 0u;
     if (tid < kSortBins + kSortClasses - 1) s_big[tid] = 0u;
     if (tid == 0) s_runs = 0u;
-    // 1. the total, so that the overflow is known before anything is written
-    // (one chunk: the scan below finds it before its first store)
-    uint64_t total = 0u;
-    for (int64_t ch = 0; n_chunks > 1 && ch < n_chunks; ++ch) {
-        load_chunk(ch * CH);
-        uint64_t sum = 0u;
+    __syncthreads();
+    // starts: each thread PER consecutive tiles
+    uint32_t c[PER];
+    uint64_t sum = 0u, total;
 #pragma unroll
-        for (int k = 0; k < PER; ++k) sum += s_c[k * 1024 + tid];
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) sum += __shfl_xor(sum, off, 64);
-        __syncthreads();
-        if (lane == 0) s_w[wave] = sum;
-        __syncthreads();
-        for (int k = 0; k < 16; ++k) total += s_w[k];
+    for (int k = 0; k < PER; ++k) {
+        c[k] = s_c[tid * PER + k];
+        sum += c[k];
     }
-    bool ovf = total > (uint64_t)capacity;  // then every range is [0, 0) and nothing is listed
-    // 2. starts and ranges (each thread PER consecutive tiles), then the bin
-    // counts (consecutive tiles on consecutive lanes: the order's queues and
-    // bins spread over the lanes)
-    uint64_t carry = 0u;
-    for (int64_t ch = 0; ch < n_chunks; ++ch) {
-        const int64_t cb = ch * CH;
-        load_chunk(cb);
-        uint32_t c[PER];
-        uint64_t sum = 0u;
+    uint64_t run = block1024_inclusive_scan(sum, s_w, total) - sum;
+    const bool ovf = total > (uint64_t)A.capacity;  // then every range is [0, 0) and nothing is listed
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            c[k] = s_c[tid * PER + k];
-            sum += c[k];
-        }
-        uint64_t incl = sum;
+    for (int k = 0; k < PER; ++k) {
+        s_st[tid * PER + k] = (uint32_t)run;
+        run += c[k];
+    }
+    __syncthreads();
+    // ranges and bin counts: consecutive tiles on consecutive lanes
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint64_t y = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += y;
+    for (int k = 0; k < PER; ++k) {
+        if (k * 1024 >= n_tiles) break;  // uniform
+        const int t = k * 1024 + tid;
+        const uint32_t c1 = ovf ? 0u : s_c[t], st = s_st[t];
+        if (t < n_tiles) {
+            A.tile_start[t] = st;
+            reinterpret_cast<uint2 *>(A.ranges)[t] = c1 ? make_uint2(st, st + c1) : make_uint2(0u, 0u);
+            if (A.order) atomicAdd(&s_cnt[(uint32_t)t % kOrderQueues][order_bin(c1)], 1u);
         }
-        __syncthreads();  // s_w of the previous chunk is read
-        if (lane == 63) s_w[wave] = incl;
-        __syncthreads();
-        uint64_t run = carry + incl - sum, chunk_total = 0u;
-        for (int k = 0; k < 16; ++k) {
-            if (k < wave) run += s_w[k];
-            chunk_total += s_w[k];
-        }
-        carry += chunk_total;
-        if (n_chunks == 1) ovf = carry > (uint64_t)capacity;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            s_st[tid * PER + k] = (uint32_t)run;
-            run += c[k];
-        }
-        __syncthreads();
-        // consecutive tiles on consecutive lanes: coalesced stores
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            if (cb + k * 1024 >= n_tiles) break;  // uniform: nothing left in the chunk
-            const int64_t t = cb + k * 1024 + tid;
-            if (t < n_tiles) {
-                const uint32_t c1 = s_c[k * 1024 + tid], st = s_st[k * 1024 + tid];
-                const bool has = c1 && !ovf;
-                tile_start[t] = st;
-                reinterpret_cast<uint2 *>(ranges)[t] = has ? make_uint2(st, st + c1) : make_uint2(0u, 0u);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            if (cb + k * 1024 >= n_tiles) break;  // uniform
-            const int64_t t = cb + k * 1024 + tid;
-            const uint32_t c1 = ovf ? 0u : s_c[k * 1024 + tid];
-            if (order && t < n_tiles) atomicAdd(&s_cnt[t % kOrderQueues][order_bin(c1)], 1u);
-            const uint32_t bin = sort_bin(c1);
-            if (c1 && bin < (uint32_t)kSortBins) atomicAdd(&s_big[bin], 1u);
-#pragma unroll
-            for (int cl = 0; cl < kSortClasses - 1; ++cl) {
-                const uint64_t m = __ballot(c1 && bin == (uint32_t)(kSortBins + cl));
-                if (lane == 0 && m) atomicAdd(&s_big[kSortBins + cl], (uint32_t)__popcll(m));
-            }
-        }
+        count_sort_bin(s_big, c1);
     }
     if (tid == 0) {
-        *d_num = (int64_t)carry;
-        *d_overflow = ovf ? 1 : 0;
+        *A.d_num = (int64_t)total;
+        *A.d_overflow = ovf ? 1 : 0;
     }
-    // 3. bin starts, then the order and the sort lists
-    if (order) order_bin_starts(s_cnt);
+    // bin starts, then the order and the sort lists
+    if (A.order) order_bin_starts(s_cnt);
     __syncthreads();
-    if (wave == 0) {
-        const uint32_t b = s_big[lane];
-        uint32_t incl = b;
+    if (tid < 64) sort_bin_starts(s_big, nullptr, s_big, A.sort_ctl);
+    __syncthreads();
+    const uint32_t qs = (uint32_t)order_stride(n_tiles);
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t y = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += y;
+    for (int k = 0; k < PER; ++k) {
+        if (k * 1024 >= n_tiles) break;  // uniform
+        const int t = k * 1024 + tid;
+        const uint32_t c1 = ovf ? 0u : s_c[t];
+        if (A.order && t < n_tiles) {
+            const uint32_t q = (uint32_t)t % kOrderQueues;
+            A.order[q * qs + atomicAdd(&s_cnt[q][order_bin(c1)], 1u)] = (uint32_t)t;
         }
-        s_big[lane] = incl - b;
-        const uint32_t n_huge = __shfl(incl - b, kHugeBins, 64);
-        if (lane == 0) sort_ctl[kSortClasses] = n_huge;
-        if (lane == 63) {
-            // the shorter classes follow the long tiles, in order
-            uint32_t at = incl;
-            sort_ctl[0] = incl;
-            for (int cl = 0; cl < kSortClasses - 1; ++cl) {
-                const uint32_t cnt = s_big[kSortBins + cl];
-                sort_ctl[1 + cl] = cnt;
-                s_big[kSortBins + cl] = at;
-                at += cnt;
-            }
-        }
+        list_tile(A, s_big, &s_runs, (uint32_t)t, c1);
     }
     __syncthreads();
-    const int64_t qs = order_stride(n_tiles);
-    for (int64_t ch = 0; ch < n_chunks; ++ch) {
-        const int64_t cb = ch * CH;
-        load_chunk(cb);
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            if (cb + k * 1024 >= n_tiles) break;  // uniform
-            const int64_t t = cb + k * 1024 + tid;
-            const bool in = t < n_tiles;
-            const uint32_t c = (ovf || !in) ? 0u : s_c[k * 1024 + tid];
-            if (order && in) {
-                const int q = (int)(t % kOrderQueues);
-                order[q * qs + atomicAdd(&s_cnt[q][order_bin(c)], 1u)] = (uint32_t)t;
-            }
-            const uint32_t bin = sort_bin(c);
-            uint32_t slot = 0u;
-#pragma unroll
-            for (int cl = 0; cl < kSortClasses - 1; ++cl) {
-                const uint32_t y = wave_append(&s_big[kSortBins + cl], c && bin == (uint32_t)(kSortBins + cl));
-                if (bin == (uint32_t)(kSortBins + cl)) slot = y;
-            }
-            if (c) sort_list[bin < (uint32_t)kSortBins ? atomicAdd(&s_big[bin], 1u) : slot] = (uint32_t)t;
-            if (c > (uint32_t)kTileSortCap) {
-                const uint32_t R = (c + kTileSortCap - 1) / kTileSortCap, r0 = atomicAdd(&s_runs, R);
-                for (uint32_t r = 0; r < R; ++r) run_list[r0 + r] = make_uint2((uint32_t)t, r);
-            }
-        }
-    }
-    __syncthreads();
-    if (tid == 0) sort_ctl[kSortClasses + 1] = s_runs;
+    if (tid == 0) A.sort_ctl[kSortClasses + 1] = s_runs;
 }
 
+// More tiles: a workgroup per 1024, in two launches.  The first counts its
+// tiles' bins and keys; the second adds up the rows of all workgroups and of
+// those before its own (a thread per column) and places its tiles.  One CU
+// walking all of them, bound by its instruction issue, took 17.2 us for 8160
+// tiles, 33.4 for 16384 and 49 for 19200; so, 10.4, 12.3 and 13.0 (two launches:
+// 3600 tiles stay with one workgroup, 8.7 us).
+constexpr int kStatBig = kOrderQueues * kOrderBins, kStatRuns = kStatBig + kSortBins + kSortClasses - 1;
+constexpr int kStatWords = kStatRuns + 3;  // then the keys (two words)
+__global__ void __launch_bounds__(1024) tile_stats_kernel(const TileScanArgs A) {
+    __shared__ uint64_t s_w[16];
+    __shared__ uint32_t s_stat[kStatWords];
+    const int tid = threadIdx.x, t = (int)blockIdx.x * 1024 + tid;
+    const uint32_t c = t < A.n_tiles ? A.tile_count[t] + (A.tile_over ? A.tile_over[t] : 0u) : 0u;
+    for (int k = tid; k < kStatWords; k += 1024) s_stat[k] = 0u;
+    __syncthreads();
+    uint64_t total;
+    (void)block1024_inclusive_scan(c, s_w, total);
+    if (t < A.n_tiles) atomicAdd(&s_stat[((uint32_t)t % kOrderQueues) * kOrderBins + order_bin(c)], 1u);
+    count_sort_bin(s_stat + kStatBig, c);
+    const uint32_t R = tile_runs(c);
+    if (R) atomicAdd(&s_stat[kStatRuns], R);
+    if (tid == 0) {
+        s_stat[kStatRuns + 1] = (uint32_t)total;
+        s_stat[kStatRuns + 2] = (uint32_t)(total >> 32);
+    }
+    __syncthreads();
+    for (int k = tid; k < kStatWords; k += 1024) A.stats[(size_t)blockIdx.x * kStatWords + k] = s_stat[k];
+}
 
-// the tile scan with chunks of PER * 1024 tiles: the smallest that holds
-// every tile, up to kScanChunk
-static hipError_t launch_tilescan(const uint32_t *tile_count, const uint32_t *tile_over, int64_t n_tiles,
-                                  int64_t capacity, uint32_t *tile_start, uint32_t *ranges, uint32_t *order,
-                                  uint32_t *sort_list, uint32_t *sort_ctl, uint2 *run_list, int64_t *d_num,
-                                  int32_t *d_overflow, hipStream_t s) {
-#define GS_TILESCAN(P)                                                                                          \
-    launch_kernel(bucket_tilescan_kernel<P>, dim3(1), dim3(1024), s, tile_count, tile_over, n_tiles, capacity, \
-                  tile_start, ranges, order, sort_list, sort_ctl, run_list, d_num, d_overflow)
-    if (n_tiles <= 1024) return GS_TILESCAN(1);
-    if (n_tiles <= 2048) return GS_TILESCAN(2);
-    if (n_tiles <= 4096) return GS_TILESCAN(4);
-    if (n_tiles <= 8192) return GS_TILESCAN(8);
-    return GS_TILESCAN(kScanChunk / 1024);
-#undef GS_TILESCAN
+__global__ void __launch_bounds__(1024) tile_place_kernel(const TileScanArgs A) {
+    static_assert(kStatWords <= 1024, "a thread per column");
+    __shared__ uint64_t s_w[16], s_total, s_first;
+    __shared__ uint32_t s_cnt[kOrderQueues][kOrderBins], s_before[kOrderQueues][kOrderBins];
+    __shared__ uint32_t s_all[kSortBins + kSortClasses - 1], s_mine[kSortBins + kSortClasses - 1];
+    __shared__ uint32_t s_big[kSortBins + kSortClasses - 1], s_runs;
+    const int tid = threadIdx.x, t = (int)blockIdx.x * 1024 + tid, n_wg = (int)gridDim.x, me = (int)blockIdx.x;
+    const uint32_t c = t < A.n_tiles ? A.tile_count[t] + (A.tile_over ? A.tile_over[t] : 0u) : 0u;
+    if (tid < kStatWords - 1) {
+        // the last column's thread takes both words of the keys
+        const bool keys = tid == kStatRuns + 1;
+        uint64_t all = 0u, before = 0u;
+        for (int r0 = 0; r0 < n_wg; r0 += 8) {
+            uint32_t lo[8], hi[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const uint32_t *row = A.stats + (size_t)min(r0 + k, n_wg - 1) * kStatWords;
+                lo[k] = row[tid];
+                hi[k] = keys ? row[tid + 1] : 0u;
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (r0 + k < n_wg) {
+                    const uint64_t v = (uint64_t)hi[k] << 32 | lo[k];
+                    all += v;
+                    if (r0 + k < me) before += v;
+                }
+        }
+        if (tid < kStatBig) {
+            (&s_cnt[0][0])[tid] = (uint32_t)all;
+            (&s_before[0][0])[tid] = (uint32_t)before;
+        } else if (tid < kStatRuns) {
+            s_all[tid - kStatBig] = (uint32_t)all;
+            s_mine[tid - kStatBig] = (uint32_t)before;
+        } else if (tid == kStatRuns) {
+            s_runs = (uint32_t)before;
+            if (me == 0) s_w[0] = all;
+        } else {
+            s_total = all;
+            s_first = before;
+        }
+    }
+    __syncthreads();
+    const bool ovf = s_total > (uint64_t)A.capacity;  // then every range is [0, 0) and nothing is listed
+    if (me == 0 && tid == 0) {
+        *A.d_num = (int64_t)s_total;
+        *A.d_overflow = ovf ? 1 : 0;
+        A.sort_ctl[kSortClasses + 1] = ovf ? 0u : (uint32_t)s_w[0];
+    }
+    if (ovf && tid < kSortBins + kSortClasses - 1) s_all[tid] = s_mine[tid] = 0u;
+    order_bin_starts(s_cnt);  // (barriers on both sides)
+    if (tid < kStatBig) (&s_cnt[0][0])[tid] += (&s_before[0][0])[tid];
+    if (tid >= 960) sort_bin_starts(s_all, s_mine, s_big, me == 0 ? A.sort_ctl : nullptr);
+    __syncthreads();
+    uint64_t total;
+    const uint32_t st = (uint32_t)(s_first + block1024_inclusive_scan(c, s_w, total) - c);
+    const uint32_t c1 = ovf ? 0u : c;
+    if (t < A.n_tiles) {
+        A.tile_start[t] = st;
+        reinterpret_cast<uint2 *>(A.ranges)[t] = c1 ? make_uint2(st, st + c1) : make_uint2(0u, 0u);
+        if (A.order) {
+            // (after an overflow the counted bins are not the lists': any order)
+            const uint32_t q = (uint32_t)t % kOrderQueues, qs = (uint32_t)order_stride(A.n_tiles);
+            A.order[q * qs + (ovf ? (uint32_t)t / kOrderQueues : atomicAdd(&s_cnt[q][order_bin(c1)], 1u))] = (uint32_t)t;
+        }
+    }
+    list_tile(A, s_big, &s_runs, (uint32_t)t, c1);
+}
+
+static hipError_t launch_tilescan(const TileScanArgs &A, hipStream_t s) {
+    if (A.n_tiles <= 1024) return launch_kernel(bucket_tilescan_kernel<1>, dim3(1), dim3(1024), s, A);
+    if (A.n_tiles <= 2048) return launch_kernel(bucket_tilescan_kernel<2>, dim3(1), dim3(1024), s, A);
+    if (A.n_tiles <= kScanTiles) return launch_kernel(bucket_tilescan_kernel<4>, dim3(1), dim3(1024), s, A);
+    const dim3 grid((unsigned)((A.n_tiles + 1023) / 1024));
+    const hipError_t e = launch_kernel(tile_stats_kernel, grid, dim3(1024), s, A);
+    return e != hipSuccess ? e : launch_kernel(tile_place_kernel, grid, dim3(1024), s, A);
 }
 
 // Ascending sorting network (bitonic) over N registers, all indices fixed at
@@ -1812,6 +1894,9 @@ SortPlan make_sort_plan(int64_t n, int64_t capacity, int64_t tiles_per_view, int
     if (p.bucket_ok) o = align256(o + sizeof(uint32_t) * (size_t)n_tiles_total);
     p.off_sctl = o;
     if (p.bucket_ok) o = align256(o + sizeof(uint32_t) * kSortCtlWords);
+    p.off_tstat = o;
+    if (p.bucket_ok && n_tiles_total > kScanTiles)
+        o = align256(o + sizeof(uint32_t) * kStatWords * (size_t)((n_tiles_total + 1023) / 1024));
     // the runs of the tiles longer than kTileSortCap (at most one per tile and one per kTileSortCap keys)
     p.off_rlist = o;
     if (p.bucket_ok)
@@ -1855,6 +1940,19 @@ static hipError_t run_bucket_sort(const SortPlan &P, const uint32_t *tt, const f
     uint32_t *slist = reinterpret_cast<uint32_t *>(ws + P.off_slist);
     uint32_t *sctl = reinterpret_cast<uint32_t *>(ws + P.off_sctl);
     uint2 *rlist = reinterpret_cast<uint2 *>(ws + P.off_rlist);
+    TileScanArgs S = {};
+    S.tile_count = tcount;
+    S.n_tiles = (int)P.n_tiles_total;
+    S.capacity = P.capacity;
+    S.tile_start = tstart;
+    S.ranges = ranges;
+    S.order = order;
+    S.sort_list = slist;
+    S.sort_ctl = sctl;
+    S.run_list = rlist;
+    S.stats = reinterpret_cast<uint32_t *>(ws + P.off_tstat);
+    S.d_num = d_num;
+    S.d_overflow = d_overflow;
     if (P.windowed) {
         // window totals and the keys outside windows start at zero (one fill:
         // the two arrays are adjacent); the counters hold offsets after the count
@@ -1866,9 +1964,8 @@ static hipError_t run_bucket_sort(const SortPlan &P, const uint32_t *tt, const f
         if ((e = launch_kernel(emit_kernel<kEmitCountWin>, dim3((unsigned)P.bucket_blocks), dim3(kEmitBlock), s,
                                A)) != hipSuccess)
             return e;
-        if ((e = launch_tilescan(tcount, A.tile_over, P.n_tiles_total, P.capacity, tstart, ranges, order, slist,
-                                 sctl, rlist, d_num, d_overflow, s)) != hipSuccess)
-            return e;
+        S.tile_over = A.tile_over;
+        if ((e = launch_tilescan(S, s)) != hipSuccess) return e;
         if ((e = launch_kernel(emit_kernel<kEmitScatterWin>, dim3((unsigned)P.bucket_blocks), dim3(kEmitBlock), s,
                                A)) != hipSuccess)
             return e;
@@ -1879,9 +1976,7 @@ static hipError_t run_bucket_sort(const SortPlan &P, const uint32_t *tt, const f
         if ((e = launch_kernel(bucket_colscan_kernel, dim3((unsigned)((P.n_tiles_total + 3) / 4)), dim3(256), s,
                                A.tile_cnt, (int)P.bucket_blocks, P.n_tiles_total, tcount)) != hipSuccess)
             return e;
-        if ((e = launch_tilescan(tcount, nullptr, P.n_tiles_total, P.capacity, tstart, ranges, order, slist, sctl,
-                                 rlist, d_num, d_overflow, s)) != hipSuccess)
-            return e;
+        if ((e = launch_tilescan(S, s)) != hipSuccess) return e;
         if ((e = launch_kernel(emit_kernel<kEmitScatterTiles>, dim3((unsigned)P.bucket_blocks), dim3(kEmitBlock), s,
                                A)) != hipSuccess)
             return e;

@@ -269,6 +269,25 @@ def test_tile_sort_depth_patterns_bit_exact(dev, orc, name, depths, V):
     _bin_sort_case(dev, B, rec, tt_o, keys_o, vals_o, ranges_o, K, V, W, H, B.make_params(W, H), K + 5, 0)
 
 
+SCAN_CASES = [
+    ("4096_tiles", [3000], 1024, 1024),   # the most that one workgroup scans
+    ("4097_tiles", [3000], 272, 3856),    # and one more: a workgroup for a single tile
+    ("9216_tiles_9_rows", [700] * 9, 512, 512),
+    ("262144_tiles_256_rows", [60] * 32, 2048, 1024),
+]
+
+
+@pytest.mark.parametrize("name,counts,W,H", SCAN_CASES, ids=[c[0] for c in SCAN_CASES])
+def test_bin_sort_tile_scan_sizes_bit_exact(dev, orc, name, counts, W, H):
+    from paper_2604_12626_amd import binding as B
+    rng = np.random.default_rng(zlib.crc32(name.encode()))
+    rec, vis = synth.synthetic_records(rng, counts, W, H)
+    tt_o, keys_o, vals_o, ranges_o, K = orc.bin_records(rec, vis, W, H, len(counts))
+    prm = B.make_params(W, H)
+    for cap, ovf in ((K, 0), (K - 1, 1)):
+        _bin_sort_case(dev, B, rec, tt_o, keys_o, vals_o, ranges_o, K, len(counts), W, H, prm, cap, ovf)
+
+
 def _bin_sort_case(dev, B, rec, tt_o, keys_o, vals_o, ranges_o, K, V, W, H, prm, cap, expect_ovf):
     import torch
     tt = torch.from_numpy(tt_o.view(np.int32).copy()).to(dev)

@@ -335,8 +335,11 @@ __global__ void __launch_bounds__(256) project_kernel(const ProjectArgs a) {
 // The same for one view and for smaller launches, where the two steps' chain
 // of latencies costs more than the lanes and the traffic they save (the rule
 // is in launch_project): one Gaussian per lane and every view in turn.
+// (Degree 3 in planes holds all 48 coefficients in flight: three waves, else it
+// spills 18 registers and writes 70 MB of scratch per million Gaussians.)
 template <int D, bool PLANES, bool ONE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 6))) project_direct_kernel(const ProjectArgs a) {
+__global__ void __launch_bounds__(256)
+    __attribute__((amdgpu_waves_per_eu(PLANES && D == 3 ? 3 : 4, 6))) project_direct_kernel(const ProjectArgs a) {
     constexpr int K = (D + 1) * (D + 1);
     extern __shared__ __attribute__((aligned(16))) char s_dyn[];  // ProjectCams[nv]
     const ProjectBlock B = project_block<ONE, false>(a, s_dyn);

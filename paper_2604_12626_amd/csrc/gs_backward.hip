@@ -125,8 +125,8 @@ __device__ __forceinline__ double moment_dyy(M &&m, double dv) {
 // Bound by the VALU (75 % of its issue; the matrix cores 25 %, the atomics
 // about 8 % of the time).  Against a 256-thread workgroup per tile whose
 // quadrants walked in step and summed with DPP adds: 16 views of 640 x 480
-// over 1.4M Gaussians 3577 -> 1600 us, a 1280 x 720 view of 1M 341 -> 196 us,
-// a 256 x 256 view of 500k in segments 52.7 -> 34.4 us.
+// over 1.4M Gaussians 3577 -> 1560 us, a 1280 x 720 view of 1M 341 -> 191 us,
+// a 256 x 256 view of 500k in segments 52.7 -> 34.3 us.
 __global__ void __launch_bounds__(64, 4) backward_tile_kernel(const BackwardTileArgs a) {
     // the chunk's staged survivors (u, v, a, b) (c, o, z, r) (g, b) and their
     // list positions inside the chunk, back to front; the batch's g and w

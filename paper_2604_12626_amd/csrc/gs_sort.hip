@@ -30,9 +30,16 @@ constexpr int kMinSortItems = 8;                    // partitions of 4096 or 819
 constexpr int kMinSortPart = kSortBlock * kMinSortItems;
 constexpr int kEmitGrid = 1024;  // emission workgroups at most (grid-stride over scan tiles beyond)
 constexpr int kBucketGrid = 256;  // emission workgroups of the bucket path (rows of the tile counters)
-constexpr int kWinGrid = 1024;    // the same with windowed counters (each a contiguous run of scan tiles)
+// the same with windowed counters (each a contiguous run of scan tiles).  The
+// runs of a launch differ in what they draw, so several a CU even out; too many
+// hand out slots too small (16 views of 640 x 480, count / scatter: 256 280 / 261
+// us, 1024 224 / 210, 2048 207 / 180, 4096 223 / 181; 64 of 256 x 256: 452 / 307,
+// 326 / 243, 330 / 235, 333 / 242).  Half as many beyond kWideGridTiles, for the
+// table's size (a row of the launch's tiles for each).
+constexpr int kWinGrid = 2048;
+constexpr int64_t kWideGridTiles = 1 << 16;
 constexpr int64_t kBucketMaxTiles = 4096;  // tiles of several views up to which one set of LDS counters holds them all
-constexpr int64_t kWindowMaxTiles = 1 << 18;  // beyond: windowed counters, up to this many (a 256 MB table)
+constexpr int64_t kWindowMaxTiles = 1 << 18;  // beyond: windowed counters, up to this many (a 1 GB table)
 constexpr int kRadixBits = 8;
 constexpr int kBins = 1 << kRadixBits;
 constexpr int kMaxPasses = 8;
@@ -1875,7 +1882,7 @@ SortPlan make_sort_plan(int64_t n, int64_t capacity, int64_t tiles_per_view, int
     p.windowed = n_tiles_total > (n_views == 1 ? (int64_t)kLdsTiles : kBucketMaxTiles);
     p.win_views = (int)(kLdsTiles / (tiles_per_view > 0 ? tiles_per_view : 1));
     p.bucket_ok = !p.windowed || (tiles_per_view <= kLdsTiles && tiles_per_view > 0 && n_tiles_total <= kWindowMaxTiles);
-    const int64_t grid = p.windowed ? kWinGrid : kBucketGrid;
+    const int64_t grid = !p.windowed ? kBucketGrid : n_tiles_total <= kWideGridTiles ? kWinGrid : kWinGrid / 2;
     p.bucket_blocks = p.scan_blocks < grid ? p.scan_blocks : grid;
     p.off_tcnt = o;
     if (p.bucket_ok) o = align256(o + sizeof(uint32_t) * (size_t)p.bucket_blocks * (size_t)n_tiles_total);

@@ -109,7 +109,8 @@ int64_t seg_offset_in_view(const gs_gaussians *segs, uint32_t mask, int s) {
     return o;
 }
 
-std::atomic<int> g_comp_groups{3};
+constexpr int kCompGroups = 3;  // the default: see the launch of gs_composite
+std::atomic<int> g_comp_groups{kCompGroups};
 std::atomic<int> g_sort_part_keys{4096};
 std::atomic<int> g_sort_lookback{16};
 std::atomic<int> g_sort_algorithm{0};
@@ -199,7 +200,7 @@ void gs_default_params(gs_params *p, int32_t width, int32_t height) {
 gs_status gs_set_tuning(const gs_tuning *t) {
     clear_error();
     if (!t) {
-        g_comp_groups.store(3);
+        g_comp_groups.store(kCompGroups);
         g_sort_part_keys.store(4096);
         g_sort_lookback.store(16);
         g_sort_algorithm.store(0);
@@ -497,7 +498,20 @@ gs_status composite_launch(const char *who, const gs_projected *proj, const uint
     const int pairs_mode = g_comp_pairs.load();
     const bool pairs =
         pairs_mode == 2 || (pairs_mode == 0 && 4 * a.n_items <= (int64_t)kPairsAutoItemsPerCu * cu_count());
-    int64_t grid = (int64_t)cu_count() * (pairs ? kPairsPerCu : g_comp_groups.load());
+    // The default number of groups is three, and four where they still find six
+    // items a wave each and a view has at least 1024 tiles: more waves hide more,
+    // but the waves of an XCD take tiles from all over, and in small views from
+    // more views, whose records no longer share its L2.  Measured, three / four:
+    // 64 views of 256 x 256 (256 tiles) 874 / 1004 us, 64 of 320 x 240 (300)
+    // 1356 / 1508, 32 of 400 x 400 (625) 1009 / 1048; 16 of 512 x 512 (1024) 644 /
+    // 606, 16 of 640 x 480 712 / 688, 8 of them 366 / 350, 4 of 1280 x 720 367 /
+    // 338, one of 1920 x 1080 195 / 185; with fewer items 4 of 640 x 480 222 / 232
+    // and 268 / 250, one of 1280 x 720 88 / 89, one of 640 x 480 56 / 63.
+    int groups = g_comp_groups.load();
+    if (groups == kCompGroups && a.T >= 1024 &&
+        4 * a.n_items >= (int64_t)6 * 4 * (kCompGroups + 1) * cu_count())
+        groups = kCompGroups + 1;
+    int64_t grid = (int64_t)cu_count() * (pairs ? kPairsPerCu : groups);
     if (grid > (pairs ? 4 : 1) * a.n_items) grid = (pairs ? 4 : 1) * a.n_items;
     if (clear_counters &&
         (e = gs::launch_fill_u32(counter, 0u, (int64_t)(kCompCounterBytes / sizeof(uint32_t)), stream)) != hipSuccess)

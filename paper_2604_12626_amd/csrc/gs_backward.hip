@@ -26,9 +26,6 @@
 
 namespace gs {
 
-
-
-
 // Sum over the wave, complete in lane 63 only, with DPP lane moves fused
 // into the adds (no LDS traffic): pairs, quads, half rows, rows (these leave
 // every lane of a 16-lane row holding the row sum), then row 0 into row 1
@@ -66,52 +63,38 @@ __device__ __forceinline__ void zero_span_grid(float *p, int64_t n) {
         q[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 }
 
-// The screen-space sums of one entry over the 64 pixels of a quadrant are a
-// product of two small matrices, and the matrix cores take them: with
+// The screen-space sums of one entry over the 64 pixels of a quadrant are
+// products of small matrices, and the matrix cores take them.  With
 //   g(e, p) = dL/dalpha * G   (0 where the entry is skipped or clamped)
 //   w(e, p) = alpha * T       (0 where it is skipped)
-// every adjoint of entry e is a combination of six moments of g over the
-// pixels (1, x, y, x^2, xy, y^2 with x, y the pixel relative to the
-// quadrant's centre) and four sums of w (times dL/dred, green, blue, depth of
-// the pixel).  A batch of kBatch entries writes its g and w rows to LDS (lane
-// = pixel), reads them back transposed as the A operand (row = entry, k =
-// pixel) and multiplies them with the pixels' ten features (B operand, in
-// registers for the whole walk): 16 v_mfma_f32_16x16x4_f32 per batch, exact
-// FP32 products accumulated in FP32.  The moments are shifted to the entry's
-// own centre in FP64 once per 64-entry chunk.  (Ten sums over the lanes with
-// DPP adds took 60 of 165 VALU instructions per entry, and the products they
-// summed another 30; this takes about 33.)
+// and (dx, dy) the pixel relative to the entry's centre, the adjoints of entry
+// e are combinations of the six sums of g dx^a dy^b, a + b <= 2, and of four
+// sums of w times dL/dred, green, blue, depth of the pixel.  A batch of kBatch
+// entries writes its g and w rows to LDS (lane = pixel) and reads them back
+// transposed:
+//  - g: a column of eight pixels a lane.  v_mfma_f32_4x4x1_16b_f32 multiplies
+//    sixteen pairs of matrices at once, one for each entry and half of the
+//    quadrant: rows are the half's four columns of pixels, k the image rows,
+//    columns 1, dy, dy^2 of the entry.  The four columns are then summed with
+//    1, dx, dx^2 in the lane.
+//  - w: rows are the entries' halves, k the pixels of a half, columns the
+//    pixels' adjoints (in registers for the whole walk): v_mfma_f32_16x16x4_f32.
+// Every term is about the entry's own centre: taken about the quadrant's and
+// shifted afterwards, with features common to all entries, sum g dx^2 of an
+// entry of about a pixel at the quadrant's corner was the difference of terms
+// some forty times its size, and lost seven bits.  Chains of FP32 roundings
+// are short (eight image rows and two pairs of columns; four times eight
+// pixels and two pairs), halves and quadrants are added in FP64.  RMS errors
+// of one quadrant's sums, of the sum of magnitudes, against 64 bits -- a sum
+// over the lanes by DPP adds / moments about the quadrant's centre / this --
+// for entries of 0.35 px^2: conic 3.4e-8 / 4.4e-6 / 3.2e-8, position 3.2e-8 /
+// 3.2e-7 / 3.0e-8; of 40 px^2: conic 1.5e-8 / 3.6e-8 / 1.5e-8.
+// (Ten sums over the lanes took 60 of 165 VALU instructions per entry, and the
+// products they summed another 30; this takes about 42 in all.)
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-constexpr int kBatch = 8;                // entries per batch: rows 0..7 are their g, rows 8..15 their w
-constexpr int kGwStride = 68;            // floats per row: the b128 reads of 16 rows fall on different banks
-enum { kM0 = 0, kMx, kMy, kMxx, kMxy, kMyy, kWr, kWg, kWb, kWz, kMoments };
-static_assert(kMoments <= 16, "the features are the columns of a 16 x 16 product");
-
-// The adjoints of an entry from its moments over one quadrant: with (du, dv)
-// the entry's centre relative to the quadrant's and dL/dP = o g,
-//   u, v: o (A sx + B sy), o (B sx + C sy)   with sx = sum g dx, sy = sum g dy
-//   conic: -o/2 sum g dx^2, -o sum g dx dy, -o/2 sum g dy^2;  opacity: sum g
-// m(k): moment k of the quadrant
-template <typename M>
-__device__ __forceinline__ double moment_dx(M &&m, double du) {
-    return (double)m(kMx) - du * (double)m(kM0);
-}
-template <typename M>
-__device__ __forceinline__ double moment_dy(M &&m, double dv) {
-    return (double)m(kMy) - dv * (double)m(kM0);
-}
-template <typename M>
-__device__ __forceinline__ double moment_dxx(M &&m, double du) {
-    return (double)m(kMxx) - du * ((double)m(kMx) + moment_dx(m, du));
-}
-template <typename M>
-__device__ __forceinline__ double moment_dxy(M &&m, double du, double dv) {
-    return (double)m(kMxy) - du * (double)m(kMy) - dv * moment_dx(m, du);
-}
-template <typename M>
-__device__ __forceinline__ double moment_dyy(M &&m, double dv) {
-    return (double)m(kMyy) - dv * ((double)m(kMy) + moment_dy(m, dv));
-}
+constexpr int kBatch = 8;      // entries per batch: rows 0..7 are their g, rows 8..15 their w
+constexpr int kGwStride = 68;  // floats per row: the b128 reads of 16 lanes fall on different banks
+enum { kS0 = 0, kSx, kSxx, kSy, kSxy, kSyy, kSums };  // sums of g dx^a dy^b
 
 // One wave per workgroup walks one 8 x 8 quadrant of a (view, tile) list, or
 // with checkpoints of one segment of one, one pixel per lane; no wave waits
@@ -122,45 +105,53 @@ __device__ __forceinline__ double moment_dyy(M &&m, double dv) {
 // adjoint), consecutive lanes on consecutive adjoints of an entry: an entry's
 // ten meet in one or two cache lines (one entry per lane took twice as long
 // as the rest of the kernel).
-// Bound by the VALU (75 % of its issue; the matrix cores 25 %, the atomics
-// about 8 % of the time).  Against a 256-thread workgroup per tile whose
-// quadrants walked in step and summed with DPP adds: 16 views of 640 x 480
-// over 1.4M Gaussians 3577 -> 1560 us, a 1280 x 720 view of 1M 341 -> 191 us,
-// a 256 x 256 view of 500k in segments 52.7 -> 34.3 us.
+// Bound by the VALU (87 % of its issue; the matrix cores 15 %).  Against a
+// 256-thread workgroup per tile whose quadrants walked in step and summed with
+// DPP adds: 16 views of 640 x 480 over 1.4M Gaussians 3577 -> 1640 us, a 1280
+// x 720 view of 1M 341 -> 195 us, a 256 x 256 view of 500k in segments 52.7 ->
+// 34.9 us (with the FP32 moments about the quadrant's centre 1571, 192, 34.3).
 __global__ void __launch_bounds__(64, 4) backward_tile_kernel(const BackwardTileArgs a) {
     // the chunk's staged survivors (u, v, a, b) (c, o, z, r) (g, b) and their
     // list positions inside the chunk, back to front; the batch's g and w
-    // rows; after the walk the first two and the rows hold the adjoints
+    // rows.  A batch's sums of g replace the first two of its survivors; after
+    // the walk the adjoints replace all of Stage, and the survivors' rows of
+    // the accumulators their positions
     struct Stage {
-        float4 e0[64], e1[64];
+        float4 e0[64], e1[64], e3[64];  // e3: sums only
         float gw[2 * kBatch][kGwStride];
     };
     __shared__ __attribute__((aligned(16))) Stage s_st;
     __shared__ float2 s_e2[64];
     __shared__ __attribute__((aligned(16))) uint32_t s_pos[64];
-    __shared__ float s_mom[kMoments][64];  // moments of the survivors
-    __shared__ uint32_t s_row[64];         // and their rows of the accumulators
+    __shared__ float s_w[2][4][64];  // sums of w over each half, times red, green, blue, depth
     static_assert(sizeof(Stage) >= 64 * kG2D * sizeof(double), "the adjoints of a chunk fit over the staging");
+    static_assert(sizeof(s_st) + sizeof(s_e2) + sizeof(s_pos) + sizeof(s_w) <= 160 * 1024 / 16,
+                  "sixteen workgroups share a CU's LDS");
     double *out = reinterpret_cast<double *>(&s_st);
+    // sum c of half h of survivor p, in floats: in e0, e1 (halves) and e3
+    auto sum_at = [](int h, int c, int p) { return (c < 4 ? 256 * h + c : 512 + 2 * h + c - 4) + 4 * p; };
+    float *sums = reinterpret_cast<float *>(&s_st);
     float4 *e0s = s_st.e0, *e1s = s_st.e1;
     float2 *e2s = s_e2;
     float(*gw)[kGwStride] = s_st.gw;
     const int lane = threadIdx.x;
     const uint64_t gt_mask = lane == 63 ? 0ull : ~0ull << (lane + 1);
-    // operand layout of v_mfma_f32_16x16x4_f32: A row / B column = lane % 16,
-    // k = lane / 16; step 4 m + c of a batch takes pixel 16 (lane / 16) + 4 m + c.
-    // Columns 0..5 are the same for every quadrant (set once), 6..9 come
-    // from the pixels' image adjoints (set per walk), the rest stay zero.
+    // a row of g or w holds pixel (x, y) of the quadrant at 8 x + y
+    const int slot_px = ((lane & 7) << 3) | (lane >> 3);
+    // v_mfma_f32_4x4x1_16b_f32: block lane / 4 (entry lane / 8 of the batch, half
+    // lane / 4 % 2); A row lane % 4 (so pixel column lane % 8), B column lane % 4;
+    // D row = register, column lane % 4.  Lane's B: 1, dy, dy^2 (columns 0, 1, 2)
+    const int g_at = (lane >> 3) * kGwStride + ((lane & 7) << 3), half = (lane >> 2) & 1, col = lane & 3;
+    const int at0 = sum_at(half, col == 0 ? kS0 : col == 1 ? kSy : kSyy, 0), at1 = sum_at(half, col == 0 ? kSx : kSxy, 0);
+    const float b1 = col == 0 ? 0.0f : 1.0f, b2 = col == 2 ? 1.0f : 0.0f, b3 = 1.0f - b2;
+    // v_mfma_f32_16x16x4_f32: A row / B column lane % 16, k = lane / 16, D row 4
+    // (lane / 16) + register, column lane % 16.  A row: entry row % 8 over half
+    // row / 8; columns 0..3 are the adjoints of the first half's pixels, 8..11
+    // of the second's (set per walk)
     const int mi = lane & 15, mk = lane >> 4;
-    const bool d_col = mi >= kWr && mi < kMoments;
-    float feat[16];
-#pragma unroll
-    for (int st = 0; st < 16; ++st) {
-        const int p = 16 * mk + st;
-        const float x = (float)(p & 7) - 3.5f, y = (float)(p >> 3) - 3.5f;
-        feat[st] = mi == kM0 ? 1.0f : mi == kMx ? x : mi == kMy ? y : mi == kMxx ? x * x : mi == kMxy ? x * y
-                 : mi == kMyy ? y * y : 0.0f;
-    }
+    const int w_at = (mi & 7) * kGwStride + 32 * (mi >> 3) + 8 * mk;
+    const bool d_col = (mi & 7) < 4;
+    float feat_d[8] = {};
     // work: quadrant (k & 3) of the (k >> 2)-th item of queue q, for workgroup
     // 8 k + q: a (view, tile) list, or with checkpoints a listed segment of one
     const uint32_t n_work = a.seg_list ? a.seg_list[0] : (uint32_t)a.n_items;
@@ -245,19 +236,20 @@ __global__ void __launch_bounds__(64, 4) backward_tile_kernel(const BackwardTile
     const uint32_t own_hi = from_end ? seg_lo + seg_len : seg_end;  // entries this walk adds
     const uint32_t seg_hi = seg_end < maxlast ? seg_end : maxlast;
     if (seg_lo >= seg_hi) continue;
-    // d . S, with S the suffix colour and depth behind the current entry over
-    // its transmittance (the background at the end of the walk, else the
-    // checkpoint at seg_end) and d the pixel's adjoint of colour and depth:
-    // the walk needs S only through this product
-    float Sr = a.bg0, Sg = a.bg1, Sb = a.bg2, Sd = 0.0f;
+    // the suffix colour and depth behind the current entry over its
+    // transmittance (the background at the end of the walk, else the
+    // checkpoint at seg_end): the walk needs the colour only through its
+    // product S with the pixel's adjoint of the colour; the depth Z, many
+    // times the colours' size, on its own, so that its rounding stays its own
+    float Sr = a.bg0, Sg = a.bg1, Sb = a.bg2, Z = 0.0f;
     if (seg_end < maxlast && ck_ok) {
         T = ck[0];
         Sr = ck[1];
         Sg = ck[2];
         Sb = ck[3];
-        Sd = ck[4];
+        Z = ck[4];
     }
-    float S = dR * Sr + dG * Sg + dB * Sb + dD * Sd;
+    float S = dR * Sr + dG * Sg + dB * Sb;
     const float dAT = dA * Tfin;
     const float amax = __builtin_canonicalizef(a.alpha_max);  // keeps the clamp's operand out of the loop
     // the image adjoints as feature columns; a pixel whose adjoint is not
@@ -266,20 +258,20 @@ __global__ void __launch_bounds__(64, 4) backward_tile_kernel(const BackwardTile
     const bool odd_px = !(isfinite(dR) && isfinite(dG) && isfinite(dB) && isfinite(dD));
     const uint64_t odd_any = __ballot(odd_px);
     {
-        float *st = &gw[0][0];
+        float *st = &gw[0][0] + slot_px;
         lds_wave_sync();
-        st[lane] = odd_px ? 0.0f : dR;
-        st[kGwStride + lane] = odd_px ? 0.0f : dG;
-        st[2 * kGwStride + lane] = odd_px ? 0.0f : dB;
-        st[3 * kGwStride + lane] = odd_px ? 0.0f : dD;
+        st[0] = odd_px ? 0.0f : dR;
+        st[kGwStride] = odd_px ? 0.0f : dG;
+        st[2 * kGwStride] = odd_px ? 0.0f : dB;
+        st[3 * kGwStride] = odd_px ? 0.0f : dD;
         lds_wave_sync();
         if (d_col) {
-            const f32x4 *src = reinterpret_cast<const f32x4 *>(st + (mi - kWr) * kGwStride + 16 * mk);
+            const f32x4 *src = reinterpret_cast<const f32x4 *>(&gw[0][0] + w_at);
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
+            for (int m = 0; m < 2; ++m) {
                 const f32x4 f = src[m];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) feat[4 * m + c] = f[c];
+                for (int c = 0; c < 4; ++c) feat_d[4 * m + c] = f[c];
             }
         }
         lds_wave_sync();
@@ -345,7 +337,7 @@ __global__ void __launch_bounds__(64, 4) backward_tile_kernel(const BackwardTile
             for (int e = 0; e < nb; e += 4) {
                 const uint4 p4 = *reinterpret_cast<const uint4 *>(&s_pos[q + e]);
                 const uint32_t pos[4] = {p4.x, p4.y, p4.z, p4.w};
-                float G[4], oG[4], at[4], r[4], c[4];
+                float G[4], oG[4], at[4], r[4], c[4], z[4];
                 bool take[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
@@ -358,75 +350,109 @@ __global__ void __launch_bounds__(64, 4) backward_tile_kernel(const BackwardTile
                     take[u] = pos[u] < last_in && !(al < a.alpha_min);
                     at[u] = take[u] ? al : 0.0f;
                     r[u] = __builtin_amdgcn_rcpf(1.0f - at[u]);  // 1 ulp reciprocal (1 where skipped)
-                    c[u] = fmaf(dR, e1.w, fmaf(dG, e2.x, fmaf(dB, e2.y, dD * e1.z)));
+                    c[u] = fmaf(dR, e1.w, fmaf(dG, e2.x, dB * e2.y));
+                    z[u] = e1.z;
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     T = T * r[u];  // transmittance in front of this entry
                     // d . (c - S): what the entry's colour and depth change
-                    const float dc = take[u] ? c[u] - S : 0.0f;
-                    const float dal = fmaf(T, dc, dAT * r[u]);
+                    const float dc = take[u] ? c[u] - S : 0.0f, dz = z[u] - Z;
+                    const float dal = fmaf(T, fmaf(dD, dz, dc), dAT * r[u]);
                     S = fmaf(at[u], dc, S);
-                    gw[e + u][lane] = take[u] && !(oG[u] > a.alpha_max) ? dal * G[u] : 0.0f;
-                    gw[kBatch + e + u][lane] = at[u] * T;
+                    Z = fmaf(at[u], dz, Z);
+                    gw[e + u][slot_px] = take[u] && !(oG[u] > a.alpha_max) ? dal * G[u] : 0.0f;
+                    gw[kBatch + e + u][slot_px] = at[u] * T;
                 }
             }
             lds_wave_sync();
-            // rows 4 mk + r, column mi: moments of entry (row mod kBatch),
-            // the first kBatch rows' g columns and the others' w columns
-            const int e4 = (4 * mk) % kBatch;
-            f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
             {
-                const f32x4 *row = reinterpret_cast<const f32x4 *>(&gw[mi][16 * mk]);
-                const f32x4 av[4] = {row[0], row[1], row[2], row[3]};
+                const f32x4 *wr = reinterpret_cast<const f32x4 *>(&gw[kBatch][0] + w_at);
+                const f32x4 wv[2] = {wr[0], wr[1]};
+                f32x4 sw[4] = {};
 #pragma unroll
-                for (int st = 0; st < 16; ++st)
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[st >> 2][st & 3], feat[st], acc, 0, 0, 0);
+                for (int st = 0; st < 8; ++st)
+                    sw[st & 3] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[st >> 2][st & 3], feat_d[st], sw[st & 3], 0, 0, 0);
+                if (d_col && (mi >> 3) == (mk >> 1)) {  // entries 4 (mk % 2) + r, over their own half
+                    const int e4 = 4 * (mk & 1);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (e4 + r < nb) s_w[mi >> 3][mi & 7][q + e4 + r] = (sw[0][r] + sw[1][r]) + (sw[2][r] + sw[3][r]);
+                }
             }
-            const bool mine = mk < 2 ? mi < kWr : d_col;
+            {
+                const int p = min(q + (lane >> 3), n - 1);  // this lane's entry (past the batch: not stored)
+                const float2 uv = *reinterpret_cast<const float2 *>(&e0s[p]);
+                const f32x4 *gr = reinterpret_cast<const f32x4 *>(&gw[0][0] + g_at);
+                const f32x4 gv[2] = {gr[0], gr[1]};
+                const float y0 = col == 0 ? 1.0f : by0 - uv.y, u0 = uv.x - (bx0 + (float)(4 * half));
+                f32x4 U = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (mine && e4 + r < nb) s_mom[mi][q + e4 + r] = acc[r];
+                for (int y = 0; y < 8; ++y) {
+                    const float dy = fmaf(b1, (float)y, y0);  // 1 in column 0
+                    U = __builtin_amdgcn_mfma_f32_4x4x1f32(gv[y >> 2][y & 3], dy * fmaf(b2, dy, b3), U, 0, 0, 0);
+                }
+                float dx[4], t[4];
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    dx[x] = (float)x - u0;
+                    t[x] = dx[x] * U[x];
+                }
+                lds_wave_sync();  // every lane has its entry's centre: the sums take its place
+                if ((lane >> 3) < nb && col < 3) {
+                    float *o = sums + 4 * p;
+                    o[at0] = (U[0] + U[1]) + (U[2] + U[3]);
+                    if (col < 2) o[at1] = (t[0] + t[1]) + (t[2] + t[3]);
+                    if (col == 0)
+                        o[at0 + kSxx] = fmaf(dx[1], t[1], dx[0] * t[0]) + fmaf(dx[3], t[3], dx[2] * t[2]);
+                }
+            }
             if (odd_any) {  // uniform; rare
                 lds_wave_sync();
                 const float dv[4] = {dR, dG, dB, dD};
                 for (int e = 0; e < nb; ++e) {
-                    const float w = gw[kBatch + e][lane];
+                    const float w = gw[kBatch + e][slot_px];
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         const float sum = wave_sum_to_last(odd_px && w != 0.0f ? w * dv[k] : 0.0f);
-                        if (lane == 63) s_mom[kWr + k][q + e] += sum;
+                        if (lane == 63) s_w[0][k][q + e] += sum;
                     }
                 }
             }
             lds_wave_sync();
         }
-        // the survivors' adjoints from their moments, each by the lane that
-        // holds its record (a walk from the list's end passes others' entries)
-        if (hit && (uint32_t)(lo + lane) < own_hi) {
-            const int pos = __popcll(bal & gt_mask);
-            auto m = [&](int j) { return s_mom[j][pos]; };
-            const double du = (double)cu - (double)(qx0 + 4), dv = (double)cv - (double)(qy0 + 4);
-            const double sx = moment_dx(m, du), sy = moment_dy(m, dv);
+        // the survivors' adjoints from their sums, each by the lane that holds
+        // its record (a walk from the list's end passes others' entries): with
+        // dL/dP = o g,
+        //   u, v: o (A sx + B sy), o (B sx + C sy)   with sx = sum g dx, sy = sum g dy
+        //   conic: -o/2 sum g dx^2, -o sum g dx dy, -o/2 sum g dy^2;  opacity: sum g
+        const int pos = __popcll(bal & gt_mask);
+        double sum[kSums];
+#pragma unroll
+        for (int c = 0; c < kSums; ++c)
+            sum[c] = hit ? (double)sums[sum_at(0, c, pos)] + (double)sums[sum_at(1, c, pos)] : 0.0;
+        lds_wave_sync();  // the adjoints take the sums' place
+        if (hit) {
             double *o = out + pos * kG2D;
-            o[kGU] = (double)co * ((double)cA * sx + (double)cB * sy);
-            o[kGV] = (double)co * ((double)cB * sx + (double)cC * sy);
-            o[kGA] = -0.5 * (double)co * moment_dxx(m, du);
-            o[kGB] = -(double)co * moment_dxy(m, du, dv);
-            o[kGC] = -0.5 * (double)co * moment_dyy(m, dv);
-            o[kGO] = (double)m(kM0);
+            if ((uint32_t)(lo + lane) < own_hi) {
+                o[kGU] = (double)co * ((double)cA * sum[kSx] + (double)cB * sum[kSy]);
+                o[kGV] = (double)co * ((double)cB * sum[kSx] + (double)cC * sum[kSy]);
+                o[kGA] = -0.5 * (double)co * sum[kSxx];
+                o[kGB] = -(double)co * sum[kSxy];
+                o[kGC] = -0.5 * (double)co * sum[kSyy];
+                o[kGO] = sum[kS0];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) o[kGR + j] = (double)m(kWr + j);
-        } else if (hit) {
-            double *o = out + __popcll(bal & gt_mask) * kG2D;
+                for (int j = 0; j < 4; ++j) o[kGR + j] = (double)s_w[0][j][pos] + (double)s_w[1][j][pos];
+            } else {
 #pragma unroll
-            for (int j = 0; j < kG2D; ++j) o[j] = 0.0;
+                for (int j = 0; j < kG2D; ++j) o[j] = 0.0;
+            }
+            s_pos[pos] = slot_of(grp, id);
         }
-        if (hit) s_row[__popcll(bal & gt_mask)] = slot_of(grp, id);
         lds_wave_sync();
         for (int i = lane; i < n * kG2D; i += 64) {
             const double v = out[i];
-            if (v != 0.0) atomicAdd(a.g2d + (size_t)s_row[i / kG2D] * kG2D + (i % kG2D), v);
+            if (v != 0.0) atomicAdd(a.g2d + (size_t)s_pos[i / kG2D] * kG2D + (i % kG2D), v);
         }
         lds_wave_sync();
     }

@@ -441,3 +441,42 @@ def test_backward_of_views_is_the_sum_over_single_views(dev, degree, V, cov):
         worst = (np.abs(got[k] - total[k]) / bound).max()
         say("  %s: %.3g of the bound" % (k, worst))
         assert worst <= 1.0, k
+
+
+@pytest.mark.parametrize("checkpoints", [False, True], ids=["whole_lists", "segmented"])
+def test_backward_of_entries_of_about_a_pixel(dev, orc, checkpoints):
+    """The sums behind the covariance's gradient for entries as small as they
+    get (the low-pass filter's 0.3 px^2 and a little), each alone at a corner
+    of a quadrant, with an image adjoint at the one pixel that holds its
+    centre, a sixteenth to three sixteenths of a pixel off: sum g dx^2 is a
+    hundredth of g, so sums about any other point than the entry's own centre
+    show.  Centres and pixels are exact in FP32 (focal length, depth and
+    offsets are powers of two), and adjoints and colours are positive, so no
+    other step cancels; the chain behind the sums is FP64.  What is left are
+    the roundings of G, alpha, the colour and the sums: 64 of 2^-24 bound them."""
+    import torch
+    from paper_2604_12626_amd import render
+    rng = np.random.default_rng(301)
+    W = H = 128
+    n = (W // 16) * (H // 16)
+    g = synth.gaussians_cube(n, rng, sh_degree=0)
+    px = np.stack([16 * (np.arange(n) % 8) + rng.integers(7, 9, n), 16 * (np.arange(n) // 8) + rng.integers(7, 9, n)])
+    off = rng.integers(1, 4, (2, n)) / 16.0 * rng.choice([-1.0, 1.0], (2, n))
+    g["means"] = np.stack([(px[0] + 0.5 + off[0] - 64) / 32, (px[1] + 0.5 + off[1] - 64) / 32, np.full(n, 2.0)],
+                          1).astype(F32)
+    g["sh"] = np.abs(g["sh"]).astype(F32)
+    G = [np.zeros((1, H, W, 3), F32), np.zeros((1, H, W), F32), np.zeros((1, H, W), F32)]
+    G[0][0, px[1], px[0]] = rng.uniform(0.5, 1.5, (n, 3))
+    G[1][0, px[1], px[0]] = rng.uniform(0.5, 1.5, n)
+    cams_np = synth.identity_camera(64.0, 64.0, 64.0, 64.0)[None]
+    tg, cams = to_dev(g, dev), torch.from_numpy(cams_np).to(dev)
+    r = render.Renderer(W, H, capacity=1 << 16, device=dev, checkpoints=checkpoints)
+    f = r.render([tg], cams, [[0]])
+    got = _np(r.backward([tg], cams, [[0]], f, *[torch.from_numpy(x).to(dev) for x in G])[0])
+    ref = orc.backward(g, cams_np, orc.params(W, H), *G, decisions=gpu_decisions(f, [0], [0], W, H))
+    _status_check(ref, W * H)
+    for k in ("log_scales", "means", "opacity"):
+        a, b = got[k].reshape(n, -1), np.asarray(ref[k], np.float64).reshape(n, -1)
+        err = np.linalg.norm(a - b, axis=1) / np.linalg.norm(b, axis=1)
+        say("  %s: error over the gradient's norm, largest %.2e, RMS %.2e" % (k, err.max(), np.sqrt(np.mean(err ** 2))))
+        assert err.max() <= 64 * 2.0 ** -24, k

@@ -130,6 +130,16 @@ class Renderer:
         self.bin_sort(f, n_views)
         self.composite(f, n_views)
 
+    def _make_host_flag(self):
+        """The overflow flag's pinned copy and its event, made once, apart from
+        the modes the caller happens to be in: an inference tensor could not be
+        written outside inference mode, and only the CPU's memory is pinned,
+        whatever the default device."""
+        if self._flag_ready is None:
+            with torch.inference_mode(False):
+                self._flag = torch.empty(1, dtype=torch.int32, device="cpu", pin_memory=True)
+            self._flag_ready = torch.cuda.Event()
+
     def _forward(self, segs, cams, view_segs, f, check, ahead):
         """All forward stages; with `check`, waits for the binning and returns
         whether it overflowed.  `ahead`: the flag is copied to the host between
@@ -143,9 +153,7 @@ class Renderer:
         if check and not ahead and int(f.overflow.item()):
             return True
         if check and ahead:
-            if self._flag is None:
-                self._flag = torch.empty(1, dtype=torch.int32, pin_memory=True)
-                self._flag_ready = torch.cuda.Event()
+            self._make_host_flag()
             self._flag.copy_(f.overflow, non_blocking=True)
             self._flag_ready.record(torch.cuda.current_stream(self.device))
         self.composite(f, n_views)

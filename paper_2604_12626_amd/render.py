@@ -64,6 +64,11 @@ class Renderer:
         self._shaped = None  # (sizes, a frame's shaped views of the buffers)
         self._flag = self._flag_ready = None  # the overflow flag on the host (pinned), and its copy's event
 
+    def __getstate__(self):
+        """Copies and pickles leave out what a frame makes again (an event can
+        be neither)."""
+        return dict(self.__dict__, _shaped=None, _flag=None, _flag_ready=None)
+
     # -- buffers ------------------------------------------------------------
     def _buf(self, name, shape, dtype, zero=False):
         t = self._bufs.get(name)

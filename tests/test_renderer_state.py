@@ -44,3 +44,26 @@ def test_render_in_a_callers_mode_and_after_it(dev, mode):
     rgb, _, _ = render.rasterize(leaf, g["log_scales"], g["quats"], g["opacity"], g["sh"], cam, r)
     rgb.sum().backward()
     assert torch.equal(rgb.detach(), want) and float(leaf.grad.abs().max()) > 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("how", ["deepcopy", "pickle"])
+def test_renderer_copies_after_frames(dev, how):
+    """A renderer that has drawn frames copies and pickles as a fresh one
+    does; the copy draws into buffers of its own."""
+    import copy
+    import pickle
+    import torch
+    from paper_2604_12626_amd import render
+    W, H, g, cam = _scene(dev)
+    r = render.Renderer(W, H, capacity=1 << 16, device=dev)
+    for _ in range(3):
+        f = r.render([g], cam)
+    want = f.rgb.clone()
+    c = copy.deepcopy(r) if how == "deepcopy" else pickle.loads(pickle.dumps(r))
+    for _ in range(3):
+        f2 = c.render([g], cam)
+        assert torch.equal(f2.rgb, want)
+    assert f2.rgb.data_ptr() != f.rgb.data_ptr()
+    f2.rgb.zero_()
+    assert torch.equal(f.rgb, want)

@@ -86,6 +86,7 @@ class Renderer:
         of a small frame's host time."""
         sizes = (n_inst, n_views, ckpt, self.capacity)
         if self._shaped is None or self._shaped[0] != sizes:
+            self._shaped = None  # or the buffers that grow would stay until all have grown
             self._shaped = (sizes, vars(self._shape_frame(n_inst, n_views, ckpt)))
         f = Frame()
         for name, t in self._shaped[1].items():
@@ -183,6 +184,7 @@ class Renderer:
         f = self.alloc_frame(n_inst, n_views, ckpt)
         if self._forward(segs, cams, view_segs, f, sync_check, ahead):
             self.capacity = min(_grow(int(f.num.item())), B.MAX_CAPACITY)
+            del f  # its buffers are freed as the larger ones are allocated
             f = self.alloc_frame(n_inst, n_views, ckpt)
             if self._forward(segs, cams, view_segs, f, sync_check, False):
                 raise RuntimeError("tile instances %d exceed the maximum capacity" % int(f.num.item()))

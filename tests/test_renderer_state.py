@@ -67,3 +67,60 @@ def test_renderer_copies_after_frames(dev, how):
     assert f2.rgb.data_ptr() != f.rgb.data_ptr()
     f2.rgb.zero_()
     assert torch.equal(f.rgb, want)
+
+
+@pytest.mark.parametrize("grow", ["sizes", "capacity"])
+def test_grown_buffers_free_the_old_ones_one_by_one(grow):
+    """While a frame of larger sizes is shaped, each buffer that grows is freed
+    when its successor is there: a renderer of a frame that its caller has
+    dropped never holds the old set and the new one together."""
+    import weakref
+    from paper_2604_12626_amd import render
+    r = render.Renderer(64, 48, capacity=1 << 12, device="cpu")
+    r.alloc_frame(1000, 1)
+    old = {k: weakref.ref(t.untyped_storage()) for k, t in r._bufs.items()}
+    seen = []
+    cut = r._buf
+
+    def buf(name, *a, **kw):
+        t = cut(name, *a, **kw)
+        if r._bufs[name].untyped_storage() is not old[name]():
+            seen.append((name, old[name]() is None))
+        return t
+
+    r._buf = buf
+    if grow == "sizes":
+        r.alloc_frame(5000, 3)
+    else:
+        r.capacity = 1 << 14
+        r.alloc_frame(1000, 1)
+    assert len(seen) >= 3 and all(freed for _, freed in seen), seen
+
+
+def test_retry_after_an_overflow_drops_the_small_frame_first():
+    """render() lets go of the frame that overflowed before it allocates the
+    larger one."""
+    import torch
+    import weakref
+    from paper_2604_12626_amd import render
+    r = render.Renderer(64, 48, capacity=1 << 12, device="cpu")
+    refs, alive, calls = [], [], []
+    alloc = r.alloc_frame
+
+    def alloc_frame(*a):
+        alive.extend(x() is not None for x in refs)
+        f = alloc(*a)
+        refs.append(weakref.ref(f))
+        return f
+
+    def forward(segs, cams, view_segs, f, check, ahead):
+        calls.append(r.capacity)
+        f.num.fill_(100_000)
+        return len(calls) == 1
+
+    r.alloc_frame, r._forward = alloc_frame, forward
+    seg = {"means": torch.zeros(10, 3), "sh_degree": 0, "opacity": torch.zeros(10), "sh": torch.zeros(10, 1, 3),
+           "log_scales": torch.zeros(10, 3), "quats": torch.zeros(10, 4)}
+    f = r.render([seg], torch.zeros(1, 16))
+    assert len(calls) == 2 and calls[1] >= 100_000 and f.keys.shape[0] == calls[1]
+    assert alive == [False]

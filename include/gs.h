@@ -170,9 +170,11 @@ void gs_default_params(gs_params *p, int32_t width, int32_t height);
 /* Launch configuration (host-side, process-wide; it changes scheduling only,
  * never a result).
  *  composite_groups_per_cu: persistent 4-wave groups per compute unit in
- *    gs_composite (1..32; at its default of 3, launches of many items of large
- *    views take 4); each wave of the grid pops (view, tile, quadrant) work
- *    items until none is left.
+ *    gs_composite (1..32); each wave of the grid pops (view, tile, quadrant)
+ *    work items until none is left.  By default automatic: 3, and 4 in launches
+ *    of many items of large views; gs_get_tuning then reports 3 with
+ *    composite_groups_auto = 1, and gs_set_tuning takes that pair as the
+ *    default again.  Any number without it is that number.
  *  sort_partition_keys: keys per onesweep partition in gs_bin_sort (4096 or
  *    8192, default 4096).
  *  sort_lookback: predecessor partitions read per round trip of the onesweep
@@ -204,7 +206,8 @@ typedef struct gs_tuning {
     int32_t sort_lookback;
     int32_t sort_algorithm;
     int32_t composite_pairs;
-    int32_t reserved[3];
+    int32_t composite_groups_auto;
+    int32_t reserved[2];
 } gs_tuning;
 gs_status gs_set_tuning(const gs_tuning *t);
 void gs_get_tuning(gs_tuning *t);

@@ -53,7 +53,13 @@ class Projected(ctypes.Structure):
 class Tuning(ctypes.Structure):
     _fields_ = [("composite_groups_per_cu", ctypes.c_int32), ("sort_partition_keys", ctypes.c_int32),
                 ("sort_lookback", ctypes.c_int32), ("sort_algorithm", ctypes.c_int32),
-                ("composite_pairs", ctypes.c_int32), ("reserved", ctypes.c_int32 * 3)]
+                ("composite_pairs", ctypes.c_int32), ("composite_groups_auto", ctypes.c_int32),
+                ("reserved", ctypes.c_int32 * 2)]
+
+
+class AutomaticGroups(int):
+    """The default composite_groups_per_cu as get_tuning reports it: equal to
+    the number it starts from, and the default again where it is set again."""
 
 
 TUNING_FIELDS = ("composite_groups_per_cu", "sort_partition_keys", "sort_lookback", "sort_algorithm",
@@ -392,6 +398,7 @@ def set_tuning(composite_groups_per_cu=None, **kw):
     t = Tuning()
     for k in TUNING_FIELDS:
         setattr(t, k, int(cur[k]))
+    t.composite_groups_auto = isinstance(cur["composite_groups_per_cu"], AutomaticGroups)
     _check(lib.gs_set_tuning(ctypes.byref(t)))
     return prev
 
@@ -399,4 +406,7 @@ def set_tuning(composite_groups_per_cu=None, **kw):
 def get_tuning():
     t = Tuning()
     load().gs_get_tuning(ctypes.byref(t))
-    return {k: int(getattr(t, k)) for k in TUNING_FIELDS}
+    cur = {k: int(getattr(t, k)) for k in TUNING_FIELDS}
+    if t.composite_groups_auto:
+        cur["composite_groups_per_cu"] = AutomaticGroups(t.composite_groups_per_cu)
+    return cur

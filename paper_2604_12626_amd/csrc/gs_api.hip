@@ -109,8 +109,8 @@ int64_t seg_offset_in_view(const gs_gaussians *segs, uint32_t mask, int s) {
     return o;
 }
 
-constexpr int kCompGroups = 3;  // the default: see the launch of gs_composite
-std::atomic<int> g_comp_groups{kCompGroups};
+constexpr int kCompGroups = 3;      // what the automatic number starts from
+std::atomic<int> g_comp_groups{0};  // 0: automatic, see the launch of gs_composite
 std::atomic<int> g_sort_part_keys{4096};
 std::atomic<int> g_sort_lookback{16};
 std::atomic<int> g_sort_algorithm{0};
@@ -200,7 +200,7 @@ void gs_default_params(gs_params *p, int32_t width, int32_t height) {
 gs_status gs_set_tuning(const gs_tuning *t) {
     clear_error();
     if (!t) {
-        g_comp_groups.store(kCompGroups);
+        g_comp_groups.store(0);
         g_sort_part_keys.store(4096);
         g_sort_lookback.store(16);
         g_sort_algorithm.store(0);
@@ -217,7 +217,8 @@ gs_status gs_set_tuning(const gs_tuning *t) {
         return fail(GS_ERR_INVALID_ARGUMENT, "sort_algorithm=%d (0 or 1)", t->sort_algorithm);
     if (t->composite_pairs < 0 || t->composite_pairs > 2)
         return fail(GS_ERR_INVALID_ARGUMENT, "composite_pairs=%d (0, 1 or 2)", t->composite_pairs);
-    g_comp_groups.store(t->composite_groups_per_cu);
+    const bool automatic = t->composite_groups_auto == 1 && t->composite_groups_per_cu == kCompGroups;
+    g_comp_groups.store(automatic ? 0 : t->composite_groups_per_cu);
     g_sort_part_keys.store(t->sort_partition_keys);
     g_sort_lookback.store(t->sort_lookback);
     g_sort_algorithm.store(t->sort_algorithm);
@@ -228,7 +229,9 @@ gs_status gs_set_tuning(const gs_tuning *t) {
 void gs_get_tuning(gs_tuning *t) {
     if (!t) return;
     memset(t, 0, sizeof(*t));
-    t->composite_groups_per_cu = g_comp_groups.load();
+    const int groups = g_comp_groups.load();
+    t->composite_groups_per_cu = groups ? groups : kCompGroups;
+    t->composite_groups_auto = groups == 0;
     t->sort_partition_keys = g_sort_part_keys.load();
     t->sort_lookback = g_sort_lookback.load();
     t->sort_algorithm = g_sort_algorithm.load();
@@ -498,19 +501,21 @@ gs_status composite_launch(const char *who, const gs_projected *proj, const uint
     const int pairs_mode = g_comp_pairs.load();
     const bool pairs =
         pairs_mode == 2 || (pairs_mode == 0 && 4 * a.n_items <= (int64_t)kPairsAutoItemsPerCu * cu_count());
-    // The default number of groups is three, and four where they still find six
+    // The automatic number of groups is three, and four where they still find six
     // items a wave each and a view has at least 1024 tiles: more waves hide more,
     // but the waves of an XCD take tiles from all over, and in small views from
     // more views, whose records no longer share its L2.  Measured, three / four:
     // 64 views of 256 x 256 (256 tiles) 874 / 1004 us, 64 of 320 x 240 (300)
     // 1356 / 1508, 32 of 400 x 400 (625) 1009 / 1048; 16 of 512 x 512 (1024) 644 /
     // 606, 16 of 640 x 480 712 / 688, 8 of them 366 / 350, 4 of 1280 x 720 367 /
-    // 338, one of 1920 x 1080 195 / 185; with fewer items 4 of 640 x 480 222 / 232
-    // and 268 / 250, one of 1280 x 720 88 / 89, one of 640 x 480 56 / 63.
+    // 338, one of 1920 x 1080 195 / 185; with fewer items neither leads: 4 of
+    // 640 x 480 222 / 232 in one room and 268 / 250 in another, one of 1280 x 720
+    // 88 / 89, one of 640 x 480 56 / 63.
     int groups = g_comp_groups.load();
-    if (groups == kCompGroups && a.T >= 1024 &&
-        4 * a.n_items >= (int64_t)6 * 4 * (kCompGroups + 1) * cu_count())
-        groups = kCompGroups + 1;
+    if (groups == 0) {
+        const bool many = a.T >= 1024 && 4 * a.n_items >= (int64_t)6 * 4 * (kCompGroups + 1) * cu_count();
+        groups = many ? kCompGroups + 1 : kCompGroups;
+    }
     int64_t grid = (int64_t)cu_count() * (pairs ? kPairsPerCu : groups);
     if (grid > (pairs ? 4 : 1) * a.n_items) grid = (pairs ? 4 : 1) * a.n_items;
     if (clear_counters &&

@@ -315,3 +315,38 @@ def test_composite_noalloc_rejects_launches_beyond_its_scratch(lib):
     st = lib.gs_composite_noalloc(C.byref(proj), None, dummy, None, 1, C.byref(p), dummy, dummy, dummy,
                                   None, None, None, 0, None)
     assert st == 1  # GS_ERR_INVALID_ARGUMENT: NULL list values
+
+
+def test_three_composite_groups_are_not_the_default():
+    """Three groups asked for are three groups (launches of many items of large
+    views take four at the default); the default, read and set again, is the
+    default again, alone and among other settings."""
+    from paper_2604_12626_amd import binding as B
+
+    def automatic():
+        t = B.Tuning()
+        B.load().gs_get_tuning(ctypes.byref(t))
+        assert t.composite_groups_per_cu == 3 and list(t.reserved) == [0, 0]
+        return t.composite_groups_auto
+
+    prev = B.get_tuning()
+    try:
+        B.set_tuning()
+        assert automatic() == 1
+        B.set_tuning(3)
+        assert automatic() == 0
+        B.set_tuning(**B.get_tuning())
+        assert automatic() == 0
+        B.set_tuning()
+        default = B.set_tuning(7, composite_pairs=1)
+        B.set_tuning(**default)
+        assert automatic() == 1
+        B.set_tuning(**dict(B.get_tuning(), sort_algorithm=1))
+        assert automatic() == 1
+        B.set_tuning(sort_algorithm=0)
+        assert automatic() == 1
+        t = B.Tuning(7, 4096, 16, 0, 0, 1)  # the flag counts for the default's number only
+        assert B.load().gs_set_tuning(ctypes.byref(t)) == 0
+        assert B.get_tuning()["composite_groups_per_cu"] == 7
+    finally:
+        B.set_tuning(**prev)

@@ -5,7 +5,6 @@
 #include <stdint.h>
 
 #include <tuple>
-#include <type_traits>
 #include <utility>
 
 #include "gs.h"

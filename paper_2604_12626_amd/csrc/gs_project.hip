@@ -8,8 +8,8 @@
 // whole cost of the visible ones (covariance, projection, spherical harmonics:
 // about 330 VALU instructions) on every wave and view, and its lanes read the
 // SH rows of scattered Gaussians 16 B at a time, again for every view.  In large
-// launches of many views each wave therefore works in two steps.  Step 1, one Gaussian per lane, 64 at a time: a
-// bound from the position and the largest scale alone (cannot_draw) rejects the
+// launches of many views of degree 3 each wave therefore works in two steps.
+// Step 1, one Gaussian per lane, 64 at a time: a bound from the position and the largest scale alone (cannot_draw) rejects the
 // pairs that surely touch no tile.  The SH rows of the Gaussians that keep a
 // view are copied to LDS once, whole rows at a time (consecutive lanes on
 // consecutive 16 B), and the kept pairs are listed there.  Step 2, one pair per
@@ -82,15 +82,13 @@ __device__ __forceinline__ bool cannot_draw(const ProjectArgs &a, const float *c
     return outside && tz > a.near_plane + 1000.0f * err;
 }
 
-// a wave's part of the LDS (NF floats per SH row, in vectors of VEC)
+// a wave's part of the LDS
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-template <int NF>
+constexpr int kShVecs = 3 * 16 / 4;         // 16-byte pieces of an SH row of degree 3
+constexpr int kShStride = kShVecs | 1;      // odd: rows start on different banks
 struct ProjectLds {
-    static constexpr int VEC = NF % 4 == 0 ? 4 : 1;
-    static constexpr int NV = NF / VEC;               // vectors per row
-    static constexpr int STRIDE = NV % 2 ? NV : NV + 1;  // odd: rows start on different banks
-    f32x4 rec[32 * 3];                                 // records on their way out, half a wave at a time
-    float sh[kRowsLds * STRIDE * VEC];
+    f32x4 rec[32 * 3];                      // records on their way out, half a wave at a time
+    f32x4 sh[kRowsLds * kShStride];
     uint2 list[128];     // kept pairs: Gaussian, view of the launch | row << 8
     uint32_t gid[kRowsLds];
     uint32_t inst[32];   // instance of a record, ~0: none
@@ -148,13 +146,11 @@ __device__ __forceinline__ void view_basis(const float *cam, float mx, float my,
     sh_basis<D>(dx, dy, dz, Y);
 }
 
-template <int D, bool PLANES>
+template <bool PLANES>
 __global__ void __launch_bounds__(256) project_kernel(const ProjectArgs a) {
-    constexpr int K = (D + 1) * (D + 1);
-    using Lds = ProjectLds<3 * K>;
-    constexpr int VEC = Lds::VEC, NV = Lds::NV, STRIDE = Lds::STRIDE;
+    constexpr int D = 3, K = 16;
     extern __shared__ __attribute__((aligned(16))) char s_dyn[];  // ProjectCams[nv]
-    __shared__ __attribute__((aligned(16))) Lds s_wave[4];
+    __shared__ __attribute__((aligned(16))) ProjectLds s_wave[4];
     const ProjectBlock B = project_block<false, true>(a, s_dyn);
     const gs_gaussians &seg = a.seg[B.k];
     const ProjectCams *s_cams = B.cams;
@@ -163,7 +159,7 @@ __global__ void __launch_bounds__(256) project_kernel(const ProjectArgs a) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const uint64_t lt_mask = (1ull << lane) - 1ull;
     const int64_t n = seg.n;
-    Lds &W = s_wave[wave];
+    ProjectLds &W = s_wave[wave];
     int listed = 0, rows = 0, copied = 0;  // pairs; rows taken, rows copied
     // component k of Gaussian i in an attribute of w components
     auto at = [&](const float *p, int64_t i, int w, int k) { return PLANES ? p[(int64_t)k * n + i] : p[w * i + k]; };
@@ -176,15 +172,14 @@ __global__ void __launch_bounds__(256) project_kernel(const ProjectArgs a) {
         const int64_t i = (int64_t)pair.x;
         const int vi = (int)(pair.y & 255u);
         // the rows not copied yet: every load in flight before the first is stored
-        using V = typename std::conditional<VEC == 4, f32x4, float>::type;
-        constexpr int IT = (kRowsLds * NV + 63) / 64;
-        const int todo = PLANES ? 0 : (rows - copied) * NV;
-        V t[IT];
+        constexpr int IT = (kRowsLds * kShVecs + 63) / 64;
+        const int todo = PLANES ? 0 : (rows - copied) * kShVecs;
+        f32x4 t[IT];
         if (todo > 0) {
 #pragma unroll
             for (int k = 0; k < IT; ++k) {
                 const int f = min(k * 64 + lane, todo - 1);
-                t[k] = reinterpret_cast<const V *>(seg.sh + (size_t)(3 * K) * W.gid[copied + f / NV])[f % NV];
+                t[k] = reinterpret_cast<const f32x4 *>(seg.sh + (size_t)(3 * K) * W.gid[copied + f / kShVecs])[f % kShVecs];
             }
         }
         const uint32_t inst = (uint32_t)(s_cams[vi].base + i);
@@ -212,7 +207,7 @@ __global__ void __launch_bounds__(256) project_kernel(const ProjectArgs a) {
 #pragma unroll
             for (int k = 0; k < IT; ++k) {
                 const int f = k * 64 + lane;
-                if (f < todo) reinterpret_cast<V *>(W.sh)[(copied + f / NV) * STRIDE + f % NV] = t[k];
+                if (f < todo) W.sh[(copied + f / kShVecs) * kShStride + f % kShVecs] = t[k];
             }
             copied = rows;
             lds_wave_sync();
@@ -232,23 +227,14 @@ __global__ void __launch_bounds__(256) project_kernel(const ProjectArgs a) {
 #pragma unroll
                 for (int f = 0; f < 3 * K; ++f) col[f % 3] += Y[f / 3] * shp[(int64_t)f * n];
             } else {
-                const float *shp = W.sh + (pair.y >> 8) * (STRIDE * VEC);
+                const f32x4 *shp = W.sh + (pair.y >> 8) * kShStride;
 #pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    float t[VEC];
-                    if constexpr (VEC == 4) {
-                        const f32x4 t4 = reinterpret_cast<const f32x4 *>(shp)[v];
-                        t[0] = t4[0];
-                        t[1] = t4[1];
-                        t[2] = t4[2];
-                        t[3] = t4[3];
-                    } else {
-                        t[0] = shp[v];
-                    }
+                for (int v = 0; v < kShVecs; ++v) {
+                    const f32x4 t4 = shp[v];
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e) {
-                        const int f = VEC * v + e;  // coefficient f = 3 k + ch
-                        col[f % 3] += Y[f / 3] * t[e];
+                    for (int e = 0; e < 4; ++e) {
+                        const int f = 4 * v + e;  // coefficient f = 3 k + ch
+                        col[f % 3] += Y[f / 3] * t4[e];
                     }
                 }
             }
@@ -332,7 +318,7 @@ __global__ void __launch_bounds__(256) project_kernel(const ProjectArgs a) {
     while (listed > 0) project(min(listed, 64));
 }
 
-// The same for one view and for smaller launches, where the two steps' chain
+// The same for few views, low degrees and smaller launches, where the two steps' chain
 // of latencies costs more than the lanes and the traffic they save (the rule
 // is in launch_project): one Gaussian per lane and every view in turn.
 // (Degree 3 in planes holds all 48 coefficients in flight: three waves, else it
@@ -426,29 +412,43 @@ __global__ void __launch_bounds__(256)
 hipError_t launch_project(ProjectArgs a, hipStream_t s) {
     if (a.n_segs == 0) return hipSuccess;
     int64_t bytes = 0;  // attributes, records and counts
+    int64_t n = 0, pairs = 0;
     int nv = 0;
+    const int K = (a.seg[0].sh_degree + 1) * (a.seg[0].sh_degree + 1);
+    const bool planes = a.seg[0].layout == GS_LAYOUT_PLANES;
     for (int k = 0; k < a.n_segs; ++k) {
-        const int views = a.first_pair[k + 1] - a.first_pair[k], K = (a.seg[k].sh_degree + 1) * (a.seg[k].sh_degree + 1);
+        const int views = a.first_pair[k + 1] - a.first_pair[k];
         bytes += a.seg[k].n * (44 + 12 * K + 52 * (int64_t)views);
+        n += a.seg[k].n;
+        pairs += a.seg[k].n * views;
         nv = std::max(nv, views);
     }
-    // Two steps win with several views, once the launch has left the 256 MB
-    // cache well behind (700k x 4 views, 310 MB, 44 us direct, 54 in two steps;
-    // 600k x 8, 390 MB, 88 / 84; 600k x 12, 515 MB, 134 / 100; 1.4M x 16 373 /
-    // 260; 8 scenes, 64 views 842 / 741).  With one view they save lanes but
-    // add latency: frames of 1M and 2M Gaussians from cold memory were 1 to 2 %
-    // slower.
-    const bool direct = nv == 1 || bytes < (int64_t)360 << 20;
+    // Two steps trade a longer chain of latencies for lanes and for the SH rows'
+    // traffic, so they win where there is much of that: at degree 3, with at
+    // least eight views a Gaussian (planes: several, whose scattered columns
+    // cost the direct kernel most), and once the launch has left the 256 MB cache
+    // well behind.  Measured in one room, direct / two steps: 8 views of 1M 159 /
+    // 143 us, 16 of 0.6M 149 / 123, 32 of 0.66M 294 / 274, 64 views of 8 scenes of
+    // very different sizes 842 / 741; below 400 MB 8 views of 0.6M 78.5 / 78.6, 16 of
+    // 0.2M 43 / 43; 2 views of 1.3M 45 / 56, 4 of 1.4M 135 / 140, 6 of 2.3M 285 / 290,
+    // 32 views of 8 equal scenes 169 / 189; degree 2: 4 views of 1.2M 85 / 98, 16 of
+    // 0.45M 73 / 85, 48 of 0.3M 153 / 180; degree 0: 16 views of 0.5M 54 / 68.  Planes
+    // of degree 3: 2 views of 1.3M 251 / 82, 16 of 0.4M 495 / 104; of degree 1: 8 of
+    // 0.9M 84 / 88.
+    const bool two_steps =
+        K == 16 && bytes >= (int64_t)400 << 20 && (planes ? nv > 1 : pairs >= 8 * n);
     a.first_block[0] = 0;
     for (int k = 0; k < a.n_segs; ++k)
         a.first_block[k + 1] = a.first_block[k] + (uint32_t)((a.seg[k].n + 255) / 256);
     const dim3 grid(a.first_block[a.n_segs]);
     const size_t lds = sizeof(ProjectCams) * (size_t)nv;
-#define GS_PROJECT(D, PLANES)                                                                                  \
-    (!direct         ? launch_kernel_lds(project_kernel<D, PLANES>, grid, dim3(256), lds, s, a)                \
-     : a.n_segs == 1 ? launch_kernel_lds(project_direct_kernel<D, PLANES, true>, grid, dim3(256), lds, s, a)   \
-                     : launch_kernel_lds(project_direct_kernel<D, PLANES, false>, grid, dim3(256), lds, s, a))
-    if (a.seg[0].layout == GS_LAYOUT_PLANES) {
+    if (two_steps)
+        return planes ? launch_kernel_lds(project_kernel<true>, grid, dim3(256), lds, s, a)
+                      : launch_kernel_lds(project_kernel<false>, grid, dim3(256), lds, s, a);
+#define GS_PROJECT(D, PLANES)                                                                                \
+    (a.n_segs == 1 ? launch_kernel_lds(project_direct_kernel<D, PLANES, true>, grid, dim3(256), lds, s, a)   \
+                   : launch_kernel_lds(project_direct_kernel<D, PLANES, false>, grid, dim3(256), lds, s, a))
+    if (planes) {
         switch (a.seg[0].sh_degree) {
             case 0: return GS_PROJECT(0, true);
             case 1: return GS_PROJECT(1, true);

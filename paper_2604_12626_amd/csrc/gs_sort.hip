@@ -1299,9 +1299,9 @@ __device__ __forceinline__ void sort_regs(uint64_t (&v)[N]) {
             }
 }
 
-// Block merge sort of the L entries at in[0, L) (L <= NT * ITEMS; entries
-// distinct and below ~0, which pads) with NT threads (tid < NT; NT = 64 and
-// ONE_WAVE for a wave on its own).  The smallest power-of-two number of
+// Block merge sort of the L entries x[m] = entry m * NT + tid (L <= NT * ITEMS;
+// entries distinct and below ~0, which pads) with NT threads (tid < NT; NT =
+// 64 and ONE_WAVE for a wave on its own).  The smallest power-of-two number of
 // threads that holds L takes ITEMS consecutive entries each and sorts them
 // in registers; then sorted runs are merged pairwise, each thread finding
 // where its ITEMS outputs start on the merge path of its pair by a binary
@@ -1311,8 +1311,8 @@ __device__ __forceinline__ void sort_regs(uint64_t (&v)[N]) {
 // value (instance) of sorted entry p to keys[p], vals[p], or the entry itself
 // to raw[p] when raw is non-NULL; reads and writes are coalesced through LDS.
 template <int NT, int ITEMS, bool ONE_WAVE>
-__device__ __forceinline__ void merge_sort_lds(uint64_t *s, const uint64_t *in, uint32_t L, uint64_t thi,
-                                               uint64_t *keys, uint32_t *vals, uint64_t *raw, uint32_t tid) {
+__device__ __forceinline__ void merge_sort_lds(uint64_t *s, uint64_t *x, uint32_t L, uint64_t thi, uint64_t *keys,
+                                               uint32_t *vals, uint64_t *raw, uint32_t tid) {
     auto slot = [](uint32_t i) { return i + i / ITEMS; };
     auto sync = [] {
         if (ONE_WAVE) lds_wave_sync();
@@ -1322,16 +1322,10 @@ __device__ __forceinline__ void merge_sort_lds(uint64_t *s, const uint64_t *in, 
     while (nt * ITEMS < L) nt <<= 1;
     const uint32_t n = nt * ITEMS;
     const bool act = tid < nt;
-    {
-        // every load issued before any is used (clamped in bounds: L >= 1)
-        uint64_t x[ITEMS];
 #pragma unroll
-        for (int m = 0; m < ITEMS; ++m) x[m] = in[min((uint32_t)m * NT + tid, L - 1u)];
-#pragma unroll
-        for (int m = 0; m < ITEMS; ++m) {
-            const uint32_t i = (uint32_t)m * NT + tid;
-            if (i < n) s[slot(i)] = i < L ? x[m] : ~0ull;
-        }
+    for (int m = 0; m < ITEMS; ++m) {
+        const uint32_t i = (uint32_t)m * NT + tid;
+        if (i < n) s[slot(i)] = i < L ? x[m] : ~0ull;
     }
     sync();
     uint64_t v[ITEMS];
@@ -1379,7 +1373,6 @@ __device__ __forceinline__ void merge_sort_lds(uint64_t *s, const uint64_t *in, 
         for (int m = 0; m < ITEMS; ++m) s[slot(tid * ITEMS + m)] = v[m];
     }
     sync();
-    uint64_t x[ITEMS];
 #pragma unroll
     for (int m = 0; m < ITEMS; ++m) x[m] = s[slot(min((uint32_t)m * NT + tid, n - 1u))];
 #pragma unroll
@@ -1396,8 +1389,8 @@ __device__ __forceinline__ void merge_sort_lds(uint64_t *s, const uint64_t *in, 
     }
 }
 
-// Spread sort of the L entries at in[0, L) (1 <= L <= NT * ITEMS, entries
-// distinct): every entry is placed near its final position by its depth
+// Spread sort of the L entries x[m] = entry m * NT + tid (the last one again past
+// the end; 1 <= L <= NT * ITEMS, entries distinct): every entry is placed near its final position by its depth
 // alone, then ranked among the few that share its bucket.  A coarse histogram
 // over COARSE equal steps of the depth bits gives the distribution of the
 // tile's depths (a wall fills a few steps, most are empty); inside its step an
@@ -1405,11 +1398,10 @@ __device__ __forceinline__ void merge_sort_lds(uint64_t *s, const uint64_t *in, 
 // entries (2^SHIFT entries a bucket), so that the buckets hold about one
 // entry each whatever the distribution: an entry meets 1.8 to 1.9 entries
 // (itself among them) in its bucket on rooms and avatars, at most 10.  Depths
-// that do not spread (many equal ones) are told by a bucket of more than
-// kSpreadMost entries: then nothing is written, false is returned, and the
-// caller merge sorts.  A dozen LDS operations per entry and ten barriers,
-// where the merge sort takes a binary search and a dependent merge per level.
-// Output as for merge_sort_lds.
+// that do not spread end in a bucket of more than kSpreadMost entries: then
+// nothing is written, false is returned, and the caller merge sorts.  A dozen
+// LDS operations per entry and ten barriers, where the merge sort takes a
+// binary search and a dependent merge per level.  Output as for merge_sort_lds.
 constexpr uint32_t kSpreadMost = 64;
 
 template <int NT, int ITEMS>
@@ -1431,7 +1423,7 @@ struct SpreadLds {
 };
 
 template <int NT, int ITEMS, bool ONE_WAVE>
-__device__ __forceinline__ bool spread_sort_lds(SpreadLds<NT, ITEMS> &M, const uint64_t *in, uint32_t L, uint64_t thi,
+__device__ __forceinline__ bool spread_sort_lds(SpreadLds<NT, ITEMS> &M, const uint64_t *x, uint32_t L, uint64_t thi,
                                                 uint64_t *keys, uint32_t *vals, uint64_t *raw, uint32_t tid) {
     using Lds = SpreadLds<NT, ITEMS>;
     constexpr int SHIFT = Lds::SHIFT, COARSE = Lds::COARSE;
@@ -1440,10 +1432,6 @@ __device__ __forceinline__ bool spread_sort_lds(SpreadLds<NT, ITEMS> &M, const u
         else __syncthreads();
     };
     const uint32_t lane = tid & 63u, wave = tid >> 6;
-    uint64_t x[ITEMS];
-#pragma unroll
-    for (int m = 0; m < ITEMS; ++m)  // loads in flight together, clamped in bounds
-        if ((uint32_t)m * NT < L) x[m] = in[min((uint32_t)m * NT + tid, L - 1u)];
     const uint32_t n_buckets = ((L - 1u) >> SHIFT) + 1u, n_words = (n_buckets + 1u) >> 1;
     for (uint32_t k = tid; k < n_words; k += NT) M.b.cnt[k] = 0u;
     for (uint32_t k = tid; k < COARSE; k += NT) M.b.coarse[k] = 0u;
@@ -1585,14 +1573,43 @@ __device__ __forceinline__ bool spread_sort_lds(SpreadLds<NT, ITEMS> &M, const u
     return true;
 }
 
-// the spread sort, or where the depths do not spread the merge sort
+// Many equal depths: whether eight of the first 64 entries' depths come again
+// among these often enough that a depth of the tile's L entries crowds a bucket
+// of the spread sort.  Every wave asks the same entries (no barrier).
+__device__ __forceinline__ bool depths_repeat(const uint64_t *in, uint32_t L, uint32_t lane) {
+    const uint32_t z = (uint32_t)(in[min(lane, L - 1u)] >> 32), looked = min(L, 64u);
+    uint32_t again = 0u;
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) {
+        const uint32_t pick = __builtin_amdgcn_readlane(z, k * looked / 8u);
+        again += (uint32_t)__popcll(__ballot(lane < L && z == pick)) - 1u;
+    }
+    return again * L > kSpreadMost * 8u * looked;
+}
+
+// The spread sort, or where the depths do not spread the merge sort (planes seen
+// frontally, quantised depths).  Binning of 16 views of 640 x 480 with lists of
+// 860 / 3440 / 6400 entries: depths that spread 444 / 1407 / 2829 us, all sorted
+// by merging 537 / 1805 / 3630 (in its own launch shapes, 512 threads for up to
+// 8192 entries); all depths equal 529 / 1885 / 4146, found out by trying the
+// spread sort first 734 / 2548 / 5121.
 template <int NT, int ITEMS, bool ONE_WAVE>
 __device__ __forceinline__ void sort_lds(SpreadLds<NT, ITEMS> &M, const uint64_t *in, uint32_t L, uint64_t thi,
                                          uint64_t *keys, uint32_t *vals, uint64_t *raw, uint32_t tid) {
-    if (spread_sort_lds<NT, ITEMS, ONE_WAVE>(M, in, L, thi, keys, vals, raw, tid)) return;
-    if (ONE_WAVE) lds_wave_sync();
-    else __syncthreads();  // the counters are read; their LDS is the merge sort's
-    merge_sort_lds<NT, ITEMS, ONE_WAVE>(M.merge, in, L, thi, keys, vals, raw, tid);
+    uint64_t x[ITEMS];
+#pragma unroll
+    for (int m = 0; m < ITEMS; ++m)  // loads in flight together, clamped in bounds
+        if ((uint32_t)m * NT < L) x[m] = in[min((uint32_t)m * NT + tid, L - 1u)];
+    if (!depths_repeat(in, L, tid & 63u)) {  // uniform
+        if (spread_sort_lds<NT, ITEMS, ONE_WAVE>(M, x, L, thi, keys, vals, raw, tid)) return;
+        if (ONE_WAVE) lds_wave_sync();
+        else __syncthreads();  // the counters are read; their LDS is the merge sort's
+    }
+    // sixteen entries a thread, unless eight hold the tile (more threads at work)
+    if (ITEMS == 16 && L <= (uint32_t)(NT * 8))
+        merge_sort_lds<NT, (ITEMS == 16 ? 8 : ITEMS), ONE_WAVE>(M.merge, x, L, thi, keys, vals, raw, tid);
+    else
+        merge_sort_lds<NT, ITEMS, ONE_WAVE>(M.merge, x, L, thi, keys, vals, raw, tid);
 }
 
 // dst[i] = f(src[i]) for i < cnt by NT threads, eight loads in flight per
@@ -1715,14 +1732,16 @@ __device__ __forceinline__ void merge_tile_runs(uint64_t *bucket, uint64_t *keys
 // entries, 256 threads: their 21 KB of LDS let seven workgroups share a CU,
 // so 1792 tiles sort in one round) and kSortLong (classes 0..2, 1024 threads,
 // a tile longer than CAP sorted as runs and merged by its own workgroup).
-// Bound by latency: a chain of LDS round trips and barriers per tile.  The
-// spread sort against merging levels: 1200 tiles of 300 entries 13.9 -> 11.6
+// Bound by latency: a chain of LDS round trips and barriers per tile, so the
+// registers are bounded to what lets as many workgroups in as the LDS (two
+// fewer of 256 threads and one of 512 cost 30 us of 444 and 160 of 1407 in the
+// frames at sort_lds).  The spread sort against merging levels: 1200 tiles of 300 entries 13.9 -> 11.6
 // us; 18.3M entries in 19200 tiles, all classes, 357 -> 237 us; 23.0M in
 // 16384 tiles 479 -> 275 us.
 constexpr int kSortShort = 5, kSortLong = 6;
 
 template <int THREADS, int CAP, int CLASS>
-__global__ void __launch_bounds__(THREADS) tile_sort_kernel(uint64_t *bucket, const uint32_t *ranges,
+__global__ void __launch_bounds__(THREADS, THREADS == 256 ? 7 : THREADS == 512 ? 6 : 4) tile_sort_kernel(uint64_t *bucket, const uint32_t *ranges,
                                                             const uint32_t *sort_list, const uint32_t *sort_ctl,
                                                             const uint2 *run_list, uint64_t *keys, uint32_t *vals,
                                                             const int32_t *d_overflow) {
@@ -1794,7 +1813,7 @@ __global__ void __launch_bounds__(THREADS) tile_merge_kernel(uint64_t *bucket, c
 
 // The tiles of 1..kTinySortCap keys: one wave each, four waves per
 // workgroup, waves striding over the list (no workgroup barriers).
-__global__ void __launch_bounds__(256) tile_sort_wave_kernel(uint64_t *bucket, const uint32_t *ranges,
+__global__ void __launch_bounds__(256, 6) tile_sort_wave_kernel(uint64_t *bucket, const uint32_t *ranges,
                                                              const uint32_t *sort_list, const uint32_t *sort_ctl,
                                                              uint64_t *keys, uint32_t *vals,
                                                              const int32_t *d_overflow) {

@@ -269,6 +269,38 @@ def test_tile_sort_depth_patterns_bit_exact(dev, orc, name, depths, V):
     _bin_sort_case(dev, B, rec, tt_o, keys_o, vals_o, ranges_o, K, V, W, H, B.make_params(W, H), K + 5, 0)
 
 
+# the tile sorts look at a tile's first 64 entries (about its first instances) to
+# tell depths that repeat: a sample that sees none of them, or nothing else
+UNEVEN_DEPTHS = [
+    ("equal_behind_the_first", lambda rng, n: np.where(np.arange(n) < 200, rng.uniform(1.0, 9.0, n), 5.0)),
+    ("equal_at_the_front", lambda rng, n: np.where(np.arange(n) < 64, 5.0, rng.uniform(1.0, 9.0, n))),
+    ("two_percent_each", lambda rng, n: 1.0 + 0.1 * rng.integers(0, 50, n)),
+]
+
+
+@pytest.mark.parametrize("V", [1, 17], ids=["few_tiles", "windowed"])
+@pytest.mark.parametrize("name,depths", UNEVEN_DEPTHS, ids=[c[0] for c in UNEVEN_DEPTHS])
+def test_tile_sort_depths_unlike_the_sample_bit_exact(dev, orc, name, depths, V):
+    """Tiles whose entries come in instance order, at the size classes' edges."""
+    from paper_2604_12626_amd import binding as B
+    rng = np.random.default_rng(124)
+    W = H = 256
+    sizes = [64, 65, 300, 513, 2048, 2049, 4097, 8193, 16384, 16385]
+    counts = [sum(sizes)] + [3] * (V - 1)
+    rec, vis = synth.synthetic_records(rng, counts, W, H)
+    vis[:] = 1
+    at = 0
+    for t, n in enumerate(sizes):
+        sel = np.arange(at, at + n)
+        at += n
+        rec[sel, 0] = 16 * t + rng.uniform(4.0, 12.0, n)
+        rec[sel, 1] = rng.uniform(4.0, 12.0, n)
+        rec[sel, 2] = depths(rng, n)
+        rec[sel, 3] = np.ones(n, np.int32).view(np.float32)
+    tt_o, keys_o, vals_o, ranges_o, K = orc.bin_records(rec, vis, W, H, V)
+    _bin_sort_case(dev, B, rec, tt_o, keys_o, vals_o, ranges_o, K, V, W, H, B.make_params(W, H), K + 5, 0)
+
+
 SCAN_CASES = [
     ("4096_tiles", [3000], 1024, 1024),   # the most that one workgroup scans
     ("4097_tiles", [3000], 272, 3856),    # and one more: a workgroup for a single tile

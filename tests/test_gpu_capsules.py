@@ -116,3 +116,38 @@ def test_capsule_queries_full_size(dev, orc):
     sample = np.union1d(sample, [len(pos) - 1])
     _check(orc, caps, first, nfr, fp, pos, nxt, aa, got, sample=sample)
     assert np.all(np.isfinite(got[0])) and np.all(got[1] >= 0) and np.all(got[2] <= got[0] + TOL)
+
+
+MANY_CASES = [
+    # name, avatars, capsules of each (of the skeleton's 23; 600: copies), agents, first avatar
+    ("920_capsules_first_3", 43, 23, 11, 3),
+    ("eight_each_of_80_avatars", 80, 8, 14, 0),
+    ("one_each_of_200_avatars", 200, 1, 24, 7),
+    ("600_each_of_2_avatars", 2, 600, 9, 0),
+]
+
+
+@pytest.mark.parametrize("name,A,n_caps,E,lo", MANY_CASES, ids=[c[0] for c in MANY_CASES])
+def test_capsule_queries_of_many_capsules(dev, orc, name, A, n_caps, E, lo):
+    """More capsules than a wave looks at before their steps (512, and of at
+    most 64 avatars): chunks that start inside an avatar, a first avatar other
+    than 0, and the least clearance carried from chunk to chunk.  In some
+    agents the nearest capsule lies in the first chunk, in some behind it."""
+    caps, first, nfr, fp, pos, nxt = _scene(51 + A, [1 + a % 3 for a in range(A)], E, [0.4 * (a % 5) for a in range(A)])
+    if n_caps <= 23:
+        caps = caps[:, :n_caps]
+    else:  # shifted copies, a metre apart
+        caps = np.concatenate([caps] * (n_caps // 23 + 1), 1)[:, :n_caps].copy()
+        shift = np.random.default_rng(9).uniform(-3.0, 3.0, (n_caps, 2))
+        shift[:23] = 0.0
+        caps[:, :, 0:2] += shift
+        caps[:, :, 4:6] += shift
+    caps = np.ascontiguousarray(caps, F32)
+    aa = np.tile([lo, A - lo], (E, 1))
+    got = _run_gpu(dev, caps, first, nfr, fp, pos, nxt, aa)
+    excl, nb = _check(orc, caps, first, nfr, fp, pos, nxt, aa, got)
+    at = got[1] - lo * n_caps  # place among the agent's capsules
+    chunk = min(512, 63 * n_caps)
+    say("capsules, %s: %d an agent, nearest in the first chunk %d, behind it %d, blocked %d" % (
+        name, (A - lo) * n_caps, (at < chunk).sum(), (at >= chunk).sum(), nb))
+    assert (A - lo) * n_caps > chunk and (at < chunk).any() and (at >= chunk).any()

@@ -113,13 +113,13 @@ BIN_CASES = [
     ("empty", [0], 32, 32),
     ("1view_640x480_200k", [200000], 640, 480),
     ("16views_256x256_60k", [4000] * 15 + [100], 256, 256),
-    # past 4096 tiles: tile counters in a window of whole views (16 of 256
-    # tiles here) that moves with the views
+    # past 4096 tiles: tile counters in a window of whole views (32 of 256
+    # tiles here)
     ("64views_256x256_windowed", [3000] * 63 + [500], 256, 256),
     # one emission block draws 40 views: the keys past its window take the
     # tiles' last slots
     ("40views_256x256_block_past_window", [90] * 40, 256, 256),
-    # 475 tiles a view: a window of 8 views, the ring wraps at 3800 tiles
+    # 475 tiles a view: a window of 17 views
     ("10views_400x300_ring", [6000] * 10, 400, 300),
 ]
 
@@ -209,10 +209,10 @@ BIG_VIEW_CASES = [
     ("1view_2048x1024_8192_tiles", [90000], 2048, 1024),
     # 8208 tiles: the onesweep sort
     ("1view_2050x1024", [30000], 2052, 1024),
-    # several such views: a window of one view that moves with them
+    # several such views: a window of one view
     ("3views_1920x1080_window_of_one", [40000, 100, 30000], 1920, 1080),
-    # 475 tiles a view: a window of 17 views, 24 views wrap its ring; then the
-    # same drawn by few instances, so that one block meets many views
+    # 475 tiles a view: a window of 17 views, of which 24 views take several; then
+    # the same drawn by few instances, so that one block meets more than it holds
     ("24views_400x300_ring", [6000] * 24, 400, 300),
     ("24views_400x300_block_past_window", [150] * 24, 400, 300),
 ]
@@ -228,6 +228,46 @@ def test_bin_sort_big_views_bit_exact(dev, orc, name, counts, W, H):
     prm = B.make_params(W, H)
     for cap, ovf in ((K, 0), (K - 1, 1)):
         _bin_sort_case(dev, B, rec, tt_o, keys_o, vals_o, ranges_o, K, len(counts), W, H, prm, cap, ovf)
+
+
+MOVING_WINDOW_CASES = [
+    # name, tiny views' sizes drawn from, views, image: over 65536 tiles in all, so
+    # at most 1024 workgroups emit
+    ("one_view", (50, 6000), 32, 1920, 1080),     # 8160 tiles a view: a window of one
+    ("two_views", (500, 9000), 60, 1024, 1024),   # 4096 tiles: a window of two
+    ("17_views", (50, 900), 400, 400, 300),       # 475 tiles: a window of 17, its ring wraps
+]
+
+
+@pytest.mark.parametrize("name,tiny,V,W,H", MOVING_WINDOW_CASES, ids=[c[0] for c in MOVING_WINDOW_CASES])
+def test_bin_sort_moving_window_bit_exact(dev, orc, name, tiny, V, W, H):
+    """Windowed tile counters where each workgroup walks three and four blocks of
+    4096 instances (13M instances, nearly all culled), so that its window of
+    views moves: runs of tiny views, whose window moves by a few views at a time
+    and keeps some, between large views with stretches of blocks that draw
+    nothing.  The smaller binning cases give every workgroup one block, whose
+    window never moves."""
+    from paper_2604_12626_amd import binding as B
+    rng = np.random.default_rng(zlib.crc32(name.encode()))
+    large = np.arange(V) % (V // 5) == V // 10  # five or six views
+    counts = rng.integers(tiny[0], tiny[1], V)
+    counts[large] = 0
+    share = rng.uniform(0.5, 1.5, large.sum())
+    counts[large] = (share / share.sum() * (13_000_000 - counts.sum())).astype(np.int64)
+    n = int(counts.sum())
+    assert V * (-(-W // 16)) * (-(-H // 16)) > 65536 and n > 3 * 1024 * 4096
+    view = np.repeat(np.arange(V, dtype=np.int32), counts)
+    drawn = rng.random(n, dtype=F32) < np.where(large, 0.004, 0.9).astype(F32)[view]
+    drawn &= (np.arange(n) // 20_000 % 3 != 0) | ~large[view]
+    idx = np.flatnonzero(drawn)
+    some, _ = synth.synthetic_records(rng, [len(idx)], W, H)
+    rec = np.zeros((n, 12), F32)
+    rec[idx] = some
+    rec[:, 11] = view.view(F32)
+    tt_o, keys_o, vals_o, ranges_o, K = orc.bin_records(rec, drawn.astype(np.uint8), W, H, V)
+    say("moving window, %s: %d of %d instances drawn, %d keys" % (name, len(idx), n, K))
+    assert K > 100_000
+    _bin_sort_case(dev, B, rec, tt_o, keys_o, vals_o, ranges_o, K, V, W, H, B.make_params(W, H), K + 3, 0)
 
 
 SORT_DEPTHS = [

@@ -732,6 +732,86 @@ def test_project_two_steps_equal_direct(dev, case):
     assert drawn > 1000  # the comparison saw records
 
 
+TWO_STEP_CASES = [
+    # name, layout, segment sizes (covariances where negative), views, skip: view v
+    # leaves out segment s where (s + v) % skip == 0
+    ("rows_5_segments", "rows", [400_003, -150_001, 1, 64, 250_007], 11, 6),
+    ("rows_more_pairs_than_a_launch", "rows", [300_001] + [60_013] * 7, 14, 9),
+    ("planes_2_views", "planes", [900_001, -500_003], 2, 99),
+]
+
+
+@pytest.mark.parametrize("name,layout,sizes,V,skip", TWO_STEP_CASES, ids=[c[0] for c in TWO_STEP_CASES])
+def test_project_two_steps_of_segments_equal_direct(dev, name, layout, sizes, V, skip):
+    """The two-step projection of launches of several segments of ragged sizes,
+    drawn by different views, and of planes, against slices of the same
+    Gaussians that take the direct kernel.  Two steps are taken at degree 3
+    from 400 MB of attributes and records and eight views a Gaussian (planes:
+    several views) on."""
+    import torch
+    from paper_2604_12626_amd import binding as B
+    rng = np.random.default_rng(4321)
+    W, H = 333, 217
+    vs = [[s for s in range(len(sizes)) if (s + v) % skip != 0] for v in range(V)]
+    views = [[v for v in range(V) if s in vs[v]] for s in range(len(sizes))]
+    segs = []
+    for n in sizes:
+        g = synth.gaussians_room(abs(n), rng, sh_degree=3)
+        if n < 0:
+            A = rng.normal(0.0, 0.02, (-n, 3, 3))
+            S = A @ np.transpose(A, (0, 2, 1))
+            del g["log_scales"], g["quats"]
+            g["cov6"] = S[:, [0, 0, 0, 1, 1, 2], [0, 1, 2, 1, 2, 2]].astype(F32)
+        segs.append(_awkward(rng, g) if abs(n) > 1000 else g)
+    # the launches: up to 8 segments and 64 (segment, view) pairs each
+    at, launches = 0, [[]]
+    for s, w in enumerate(views):
+        for v in w:
+            if at == 64:
+                launches.append([])
+                at = 0
+            launches[-1].append(s)
+            at += 1
+    first = [(s, launches[0].count(s)) for s in set(launches[0])]
+    assert sum(abs(sizes[s]) * (44 + 12 * 16 + 52 * w) for s, w in first) >= 400 << 20
+    assert layout == "planes" or sum(abs(sizes[s]) * (w - 8) for s, w in first) >= 0
+    cams = torch.from_numpy(np.stack([synth.camera_room(rng, W, H) for _ in range(V)])).to(dev)
+    prm = B.make_params(W, H)
+
+    def project(some, view_segs, c):
+        t = [to_dev(_planes(g) if layout == "planes" else g, dev) for g in some]
+        total = B.instance_offsets(t, view_segs)[-1]
+        tt = torch.full((total,), -7, dtype=torch.int32, device=dev)
+        rec = torch.zeros((total, 12), dtype=torch.float32, device=dev)
+        B.project(t, c, view_segs, prm, tt, rec)
+        torch.cuda.synchronize()
+        return tt, rec
+
+    tt, rec = project(segs, vs, cams)
+    place, at = {}, 0  # first instance of a segment in a view
+    for v in range(V):
+        for s in vs[v]:
+            place[v, s] = at
+            at += abs(sizes[s])
+    drawn = 0
+    for s, g in enumerate(segs):
+        m, w = len(g["means"]), views[s]
+        for a in range(0, m, 30_011):
+            b = min(m, a + 30_011)
+            part = {k: (np.ascontiguousarray(x[a:b]) if isinstance(x, np.ndarray) else x) for k, x in g.items()}
+            ts, rs = project([part], [[0]] * len(w), cams[w].contiguous())
+            for k, v in enumerate(w):
+                i, j = slice(place[v, s] + a, place[v, s] + b), slice(k * (b - a), (k + 1) * (b - a))
+                assert torch.equal(tt[i], ts[j])
+                vis = ts[j] > 0
+                drawn += int(vis.sum())
+                want = rs[j][vis].view(torch.int32)
+                want[:, 11] = v
+                assert torch.equal(rec[i][vis].view(torch.int32), want)
+    say("two-step projection, %s: %d of %d drawn" % (name, drawn, at))
+    assert drawn > 1000
+
+
 def test_project_many_segments_share_launches(dev):
     """Eleven segments of mixed degrees drawn by nine views (more segments and
     (segment, view) pairs than one launch takes, some views without some

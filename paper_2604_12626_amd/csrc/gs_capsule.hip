@@ -174,8 +174,11 @@ __global__ void __launch_bounds__(256) capsule_query_kernel(const CapsuleArgs a)
             const float4 *c1 = reinterpret_cast<const float4 *>(a.caps + ((size_t)r1 * a.n_caps + c) * 8);
             const float4 x0 = c0[0], y0 = c0[1], x1 = c1[0], y1 = c1[1];
             const float t1 = 1.0f - s;
-            // fused as written, not as the compiler would here: the last bit
-            // decides the nearest of two capsules that are equally near
+            // Fused as written, so that the last bit, which decides the nearest of
+            // two equally near capsules, stays what it has always been: that is
+            // how the compiler once fused the plain expression, cb.z alone with
+            // the other product inside.  It is no slip: with that component like
+            // its neighbours, 1 of 4096 nearest capsules was another one.
             ca = v3(fmaf(s, x1.x, t1 * x0.x), fmaf(s, x1.y, t1 * x0.y), fmaf(s, x1.z, t1 * x0.z));
             const V3 cb = v3(fmaf(s, y1.x, t1 * y0.x), fmaf(s, y1.y, t1 * y0.y), fmaf(t1, y0.z, s * y1.z));
             r = fmaf(s, x1.w, t1 * x0.w);

@@ -180,7 +180,10 @@ class Renderer:
         ckpt = (n_views * self.T <= self.AUTO_CHECKPOINT_ITEMS) if mode == "auto" else bool(mode)
         n_inst = B.instance_offsets(segs, view_segs)[-1]
         # the capacity has held a frame of these sizes: expect it to hold this one
-        ahead = self._shaped is not None and self._shaped[0] == (n_inst, n_views, ckpt, self.capacity)
+        # (not under capture, where the check is refused at the flag's first read,
+        # with a capture that can still be ended)
+        ahead = (self._shaped is not None and self._shaped[0] == (n_inst, n_views, ckpt, self.capacity)
+                 and not torch.cuda.is_current_stream_capturing())
         f = self.alloc_frame(n_inst, n_views, ckpt)
         if self._forward(segs, cams, view_segs, f, sync_check, ahead):
             self.capacity = min(_grow(int(f.num.item())), B.MAX_CAPACITY)

@@ -69,6 +69,26 @@ def test_renderer_copies_after_frames(dev, how):
     assert torch.equal(f.rgb, want)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("frames", [1, 2, 3])
+def test_checked_render_under_capture_is_refused_and_leaves_the_gpu_usable(dev, frames):
+    """render() checks for an overflow, which needs the GPU's answer: under
+    capture it is refused, the capture ends, and eager frames go on."""
+    import torch
+    from paper_2604_12626_amd import render
+    W, H, g, cam = _scene(dev)
+    r = render.Renderer(W, H, capacity=1 << 16, device=dev)
+    for _ in range(frames):
+        want = r.render([g], cam).rgb.clone()
+    torch.cuda.synchronize()
+    with pytest.raises(RuntimeError, match="capturing"):
+        with torch.cuda.graph(torch.cuda.CUDAGraph()):
+            r.render([g], cam)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        assert torch.equal(r.render([g], cam).rgb, want)
+
+
 @pytest.mark.parametrize("grow", ["sizes", "capacity"])
 def test_grown_buffers_free_the_old_ones_one_by_one(grow):
     """While a frame of larger sizes is shaped, each buffer that grows is freed

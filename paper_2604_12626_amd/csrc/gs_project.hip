@@ -424,19 +424,22 @@ hipError_t launch_project(ProjectArgs a, hipStream_t s) {
         nv = std::max(nv, views);
     }
     // Two steps trade a longer chain of latencies for lanes and for the SH rows'
-    // traffic, so they win where there is much of that: at degree 3, with at
-    // least eight views a Gaussian (planes: several, whose scattered columns
-    // cost the direct kernel most), and once the launch has left the 256 MB cache
-    // well behind.  Measured in one room, direct / two steps: 8 views of 1M 159 /
-    // 143 us, 16 of 0.6M 149 / 123, 32 of 0.66M 294 / 274, 64 views of 8 scenes of
-    // very different sizes 842 / 741; below 400 MB 8 views of 0.6M 78.5 / 78.6, 16 of
-    // 0.2M 43 / 43; 2 views of 1.3M 45 / 56, 4 of 1.4M 135 / 140, 6 of 2.3M 285 / 290,
-    // 32 views of 8 equal scenes 169 / 189; degree 2: 4 views of 1.2M 85 / 98, 16 of
-    // 0.45M 73 / 85, 48 of 0.3M 153 / 180; degree 0: 16 views of 0.5M 54 / 68.  Planes
-    // of degree 3: 2 views of 1.3M 251 / 82, 16 of 0.4M 495 / 104; of degree 1: 8 of
-    // 0.9M 84 / 88.
-    const bool two_steps =
-        K == 16 && bytes >= (int64_t)400 << 20 && (planes ? nv > 1 : pairs >= 8 * n);
+    // traffic, so they win where there is much of that: at degree 3, with eight to
+    // twenty-four views a Gaussian (with more, nearly every Gaussian is kept by some
+    // view and the direct kernel's reads serve many), planes with several, whose
+    // scattered columns cost it most; and once the launch has left the 256 MB cache
+    // well behind.  Measured in two rooms, direct / two steps, us: 8 views of 0.8M
+    // 134 / 110 and 101 / 92, 16 of 0.8M 217 / 209 and 172 / 162, 24 of 0.4M 141 /
+    // 111 and 148 / 121, 64 views of 8 scenes of very different sizes 842 / 741; 32
+    // of 0.4M 178 / 165 and 211 / 222, 48 of 0.4M 273 / 291 and 310 / 334, 64 of 0.4M
+    // 371 / 407 and 402 / 445; below 400 MB 8 views of 0.4M 50 / 53 and 42 / 48, 16 of
+    // 0.2M 51 / 48 and 45 / 40; 2 views of 1.3M 45 / 56, 4 of 1.4M 135 / 140, 6 of 2.3M
+    // 285 / 290, 32 views of 8 equal scenes 169 / 189; degree 2: 4 views of 1.2M 85 /
+    // 98, 16 of 0.45M 73 / 85, 48 of 0.3M 153 / 180; degree 0: 16 views of 0.5M 54 / 68.
+    // Planes of degree 3: 2 views of 1.3M 251 / 82, 16 of 0.4M 495 / 104, 64 of 0.35M
+    // 1602 / 342; of degree 1: 8 of 0.9M 84 / 88.
+    const bool two_steps = K == 16 && bytes >= (int64_t)400 << 20 &&
+                           (planes ? nv > 1 : pairs >= 8 * n && pairs <= 24 * n);
     a.first_block[0] = 0;
     for (int k = 0; k < a.n_segs; ++k)
         a.first_block[k + 1] = a.first_block[k] + (uint32_t)((a.seg[k].n + 255) / 256);

@@ -746,8 +746,8 @@ def test_project_two_steps_of_segments_equal_direct(dev, name, layout, sizes, V,
     """The two-step projection of launches of several segments of ragged sizes,
     drawn by different views, and of planes, against slices of the same
     Gaussians that take the direct kernel.  Two steps are taken at degree 3
-    from 400 MB of attributes and records and eight views a Gaussian (planes:
-    several views) on."""
+    from 400 MB of attributes and records on and with eight to twenty-four views
+    a Gaussian (planes: several views)."""
     import torch
     from paper_2604_12626_amd import binding as B
     rng = np.random.default_rng(4321)

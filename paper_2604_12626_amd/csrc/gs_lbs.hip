@@ -198,13 +198,16 @@ __device__ __forceinline__ Blend4 blend_of(const LbsArgs &a, int64_t i) {
 // output in LDS (where it fits, kJointLds floats), whose nonzero entries end
 // in float atomics.  A group that spans avatars takes one product per avatar,
 // up to four; the Gaussians of further ones add their 48 terms themselves
-// (avatars mixed at random would take a product per Gaussian).  So does a
-// Gaussian whose dA is not finite, which would reach every joint of the
-// product through the zero weights.  Bound by its 140 B of reads per Gaussian
-// and their latency; adding every element to LDS with atomics (48 per
-// Gaussian, a few lanes of a wave on the same joint each time) took 114 us
-// for 400k Gaussians of 8 avatars with 24 joints, this takes 25 us.
+// (avatars mixed at random would take a product per Gaussian), and in small
+// calls, where the products' chain is the time, all of a group of more than
+// sixteen avatars (1000 Gaussians of 64 avatars of 55 joints mixed 36 us with
+// them, 32 without).  So does a Gaussian whose dA is not finite, which would
+// reach every joint of the product through the zero weights.  Bound by its 140
+// B of reads per Gaussian and their latency; adding every element to LDS with
+// atomics (48 per Gaussian, a few lanes of a wave on the same joint each time)
+// took 114 us for 400k Gaussians of 8 avatars with 24 joints, this takes 25 us.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int kFewGroups = 64;  // groups of a small call
 constexpr int kJgStride = 68;  // floats per row of 64 Gaussians: rows on different banks
 template <int MB, int WAVES>
 __global__ void __launch_bounds__(64 * WAVES) lbs_joint_mfma_kernel(const LbsArgs a, float *d_skin) {
@@ -263,7 +266,14 @@ __global__ void __launch_bounds__(64 * WAVES) lbs_joint_mfma_kernel(const LbsArg
 #pragma unroll
         for (int e = 0; e < 12; ++e) dAs[e][lane] = finite ? dA[e] : 0.0f;
         uint64_t left = __ballot(valid && finite);
-        for (int turn = 0; left && turn < 4; ++turn) {  // one avatar at a time
+        int turns = 4;
+        if (groups <= kFewGroups) {  // uniform
+            uint64_t m = left;
+            for (int k = 0; m && k < 16; ++k)
+                m &= ~__ballot(bl.av == __builtin_amdgcn_readlane(bl.av, __ffsll((unsigned long long)m) - 1));
+            if (m) turns = 0;
+        }
+        for (int turn = 0; left && turn < turns; ++turn) {  // one avatar at a time
             const int av = __builtin_amdgcn_readlane(bl.av, __ffsll((unsigned long long)left) - 1);
             const bool mine = valid && finite && bl.av == av;
             left &= ~__ballot(mine);
@@ -352,8 +362,14 @@ hipError_t launch_lbs_joint_grad(const LbsArgs &a, float *d_skin, int n_cu, hipS
         const int64_t g = ((a.n + 63) / 64 + waves - 1) / waves;
         return dim3((unsigned)(g < n_cu ? g : n_cu));
     };
-    if (a.n_joints <= 16) return launch_kernel(lbs_joint_mfma_kernel<1, 8>, grid(8), dim3(512), s, a, d_skin);
-    if (a.n_joints <= 32) return launch_kernel(lbs_joint_mfma_kernel<2, 8>, grid(8), dim3(512), s, a, d_skin);
+    // Half as many while that leaves a wave for every group on as many CUs: eight
+    // contend for a CU's LDS while others are idle (24 joints, 8 avatars, 20 k
+    // Gaussians 19.0 / 15.8 us, mixed at random 40.4 / 27.4; 60 k 18.5 / 15.8).
+    const bool few = (a.n + 63) / 64 <= 4 * (int64_t)n_cu;
+    if (a.n_joints <= 16 && !few) return launch_kernel(lbs_joint_mfma_kernel<1, 8>, grid(8), dim3(512), s, a, d_skin);
+    if (a.n_joints <= 32 && !few) return launch_kernel(lbs_joint_mfma_kernel<2, 8>, grid(8), dim3(512), s, a, d_skin);
+    if (a.n_joints <= 16) return launch_kernel(lbs_joint_mfma_kernel<1, 4>, grid(4), dim3(256), s, a, d_skin);
+    if (a.n_joints <= 32) return launch_kernel(lbs_joint_mfma_kernel<2, 4>, grid(4), dim3(256), s, a, d_skin);
     if (a.n_joints <= 64) return launch_kernel(lbs_joint_mfma_kernel<4, 4>, grid(4), dim3(256), s, a, d_skin);
     return launch_kernel(lbs_joint_grad_kernel, grid(4), dim3(256), s, a, d_skin);
 }

@@ -1073,6 +1073,39 @@ def test_lbs_joint_matrix_gradient_parity(dev, orc, n_avatars):
     assert np.all(got[ref == 0] == 0)  # joints no Gaussian blends stay exactly zero
 
 
+@pytest.mark.parametrize("J", [9, 24, 40])
+@pytest.mark.parametrize("n,A", [(70_001, 3), (70_001, 30), (4096, 40), (4097, 40), (65, 20)],
+                         ids=["eight_waves", "eight_waves_mixed", "small_mixed", "past_small_mixed", "two_groups"])
+def test_lbs_joint_matrix_gradient_call_sizes(dev, orc, n, A, J):
+    """Joint-matrix gradients of calls large enough for eight waves a workgroup,
+    and of small ones whose groups of 64 hold more than sixteen avatars, drawn
+    at random.  A joint sums FP32 terms of either sign in chains of at most n /
+    A of them: 2e-4 of the largest bounds that as in the tests beside."""
+    import torch
+    from paper_2604_12626_amd import binding as B
+    rng = np.random.default_rng(2000 + J + n)
+    aof = rng.integers(0, A, n).astype(np.int32)
+    g = synth.gaussians_cube(n, rng)
+    g["joint_idx"] = rng.integers(0, J, (n, 4)).astype(np.uint8)
+    g["weights"] = rng.dirichlet(np.ones(4), size=n).astype(F32)
+    skin = (np.eye(3, 4).reshape(12) + 0.2 * rng.standard_normal((A, J, 12))).astype(F32)
+    gm = rng.standard_normal((n, 3)).astype(F32)
+    gc = (rng.standard_normal((n, 6)) * 1e3).astype(F32)
+    t = to_dev(g, dev)
+    out = torch.full((A, J, 12), 7.0, device=dev)
+    B.deform_lbs_backward_joints(t["means"], t["log_scales"], t["quats"], t["joint_idx"], t["weights"],
+                                 torch.from_numpy(aof).to(dev), torch.from_numpy(skin).to(dev),
+                                 torch.from_numpy(gm).to(dev), torch.from_numpy(gc).to(dev), out)
+    torch.cuda.synchronize()
+    ref = orc.lbs_backward_joints(g["means"], g["log_scales"], g["quats"], orc.dense_weights(g["joint_idx"],
+                                  g["weights"], J), aof, skin, J, gm, gc)
+    got = out.cpu().numpy().astype(np.float64)
+    err = np.abs(got - ref).max() / np.abs(ref).max()
+    say("joint gradients, n %d, %d avatars, %d joints: %.2e of the largest" % (n, A, J, err))
+    assert err <= 2e-4
+    assert np.all(got[ref == 0] == 0)
+
+
 @pytest.mark.parametrize("J", [1, 16, 17, 32, 33, 64, 65])
 def test_lbs_joint_matrix_gradient_joint_counts(dev, orc, J):
     """Joint-matrix gradients at the edges of the matrix product's row blocks

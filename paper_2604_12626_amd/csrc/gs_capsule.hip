@@ -117,9 +117,14 @@ __device__ __forceinline__ void take_min(float &g, int &i, float g2, int i2) {
 // 12.1 us.
 constexpr int kCapChunk = 512;  // capsules of an agent looked at before their steps
 
-__global__ void __launch_bounds__(256) capsule_query_kernel(const CapsuleArgs a) {
-    __shared__ float s_least[4][kCapChunk];
-    __shared__ uint16_t s_list[4][kCapChunk];
+// ROUND: no agent has more capsules than lanes, and there are many agents: each
+// lane asks its capsule for both, which saves the second round and registers
+// (launch_capsule_queries).
+template <bool ROUND>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ROUND ? 7 : 6)))
+capsule_query_kernel(const CapsuleArgs a) {
+    __shared__ float s_least[4][ROUND ? 1 : kCapChunk];
+    __shared__ uint16_t s_list[4][ROUND ? 1 : kCapChunk];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t e = (int64_t)blockIdx.x * 4 + wave;
     if (e >= a.n_agents) return;  // whole waves leave together
@@ -192,11 +197,13 @@ __global__ void __launch_bounds__(256) capsule_query_kernel(const CapsuleArgs a)
             if (j >= m) continue;
             const float g = sqrtf(seg_seg_dist2(p0, up, ca, cd)) - a.radius - r;
             take_min(best, best_i, g, lo * a.n_caps + base + j);
-            if (step)  // the least gap its swept step can have
+            if (ROUND && step)
+                best_step = fminf(best_step, seg_parallelogram_dist(ca, cd, p0, sd, up) - a.radius - r);
+            if (!ROUND && step)  // the least gap its swept step can have
                 s_least[wave][j] = g - 1.001f * sdl - 2e-3f * (a.height + sqrtf(dot(cd, cd)) + sdl) -
                                    1e-5f * fabsf(g) - far;
         }
-        if (!step) continue;  // uniform
+        if (ROUND || !step) continue;  // uniform
         float least = best;
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) least = fminf(least, __shfl_xor(least, off, 64));
@@ -239,7 +246,13 @@ __global__ void __launch_bounds__(256) capsule_query_kernel(const CapsuleArgs a)
 hipError_t launch_capsule_queries(const CapsuleArgs &a, hipStream_t s) {
     if (a.n_agents <= 0) return hipSuccess;
     const unsigned grid = (unsigned)((a.n_agents + 3) / 4);
-    return launch_kernel(capsule_query_kernel, dim3(grid), dim3(256), s, a);
+    // With more agents than the CUs hold at once the second round's work counts,
+    // with fewer only its latency, which the steps of a few lanes make up for (one
+    // round / two, 23 capsules: 65536 agents 77 / 88 us, 16384 23.7 / 26.8, 4096 11.0
+    // / 11.0, 1024 11.5 / 9.3; 46 capsules 80 / 88, 24.8 / 26.9, 11.0 / 11.1).
+    if ((int64_t)a.n_avatars * a.n_caps <= 64 && a.n_agents >= 8192)
+        return launch_kernel(capsule_query_kernel<true>, dim3(grid), dim3(256), s, a);
+    return launch_kernel(capsule_query_kernel<false>, dim3(grid), dim3(256), s, a);
 }
 
 }  // namespace gs

@@ -151,3 +151,23 @@ def test_capsule_queries_of_many_capsules(dev, orc, name, A, n_caps, E, lo):
     say("capsules, %s: %d an agent, nearest in the first chunk %d, behind it %d, blocked %d" % (
         name, (A - lo) * n_caps, (at < chunk).sum(), (at >= chunk).sum(), nb))
     assert (A - lo) * n_caps > chunk and (at < chunk).any() and (at >= chunk).any()
+
+
+@pytest.mark.parametrize("A,n_caps", [(2, 23), (64, 1), (3, 21)])
+def test_capsule_queries_of_many_agents_and_few_capsules(dev, A, n_caps):
+    """8192 agents and more with at most 64 capsules in all take one round of
+    lanes; the same agents in two calls of fewer take two: every output equal
+    bit for bit."""
+    caps, first, nfr, fp, pos, nxt = _scene(71, [1 + a % 4 for a in range(A)], 400, [0.3 * (a % 9) for a in range(A)])
+    caps = np.ascontiguousarray(caps[:, :n_caps])
+    rng = np.random.default_rng(72)
+    E = 8195
+    pos = np.tile(pos, (21, 1))[:E] + rng.normal(0.0, 0.05, (E, 3)).astype(F32)
+    nxt = np.tile(nxt, (21, 1))[:E]
+    aa = np.stack([rng.integers(-1, A, E), rng.integers(0, A + 1, E)], 1)
+    whole = _run_gpu(dev, caps, first, nfr, fp, pos, nxt, aa)
+    half = [_run_gpu(dev, caps, first, nfr, fp, pos[s], nxt[s], aa[s]) for s in (slice(0, 4097), slice(4097, E))]
+    say("capsules, %d x %d: %d blocked" % (A, n_caps, int((whole[3] == 1).sum())))
+    assert 0 < int((whole[3] == 1).sum()) < E
+    for k in range(4):
+        assert np.array_equal(whole[k], np.concatenate([half[0][k], half[1][k]]))

@@ -1575,7 +1575,9 @@ __device__ __forceinline__ bool spread_sort_lds(SpreadLds<NT, ITEMS> &M, const u
 
 // Many equal depths: whether eight of the first 64 entries' depths come again
 // among these often enough that a depth of the tile's L entries crowds a bucket
-// of the spread sort.  Every wave asks the same entries (no barrier).
+// of the spread sort.  Every wave asks the same entries (no barrier).  Not asked
+// in a single wave's short lists, where it costs 2 to 3 % (60 views of 640 x 480,
+// 290 / 297 us) and trying in vain no more than merging alone took (197 / 196).
 __device__ __forceinline__ bool depths_repeat(const uint64_t *in, uint32_t L, uint32_t lane) {
     const uint32_t z = (uint32_t)(in[min(lane, L - 1u)] >> 32), looked = min(L, 64u);
     uint32_t again = 0u;
@@ -1600,7 +1602,7 @@ __device__ __forceinline__ void sort_lds(SpreadLds<NT, ITEMS> &M, const uint64_t
 #pragma unroll
     for (int m = 0; m < ITEMS; ++m)  // loads in flight together, clamped in bounds
         if ((uint32_t)m * NT < L) x[m] = in[min((uint32_t)m * NT + tid, L - 1u)];
-    if (!depths_repeat(in, L, tid & 63u)) {  // uniform
+    if (ONE_WAVE || !depths_repeat(in, L, tid & 63u)) {  // uniform
         if (spread_sort_lds<NT, ITEMS, ONE_WAVE>(M, x, L, thi, keys, vals, raw, tid)) return;
         if (ONE_WAVE) lds_wave_sync();
         else __syncthreads();  // the counters are read; their LDS is the merge sort's
@@ -1896,7 +1898,11 @@ SortPlan make_sort_plan(int64_t n, int64_t capacity, int64_t tiles_per_view, int
     // 1080 view of 2M Gaussians, 8160 tiles: binning 180 us against 383 by the
     // onesweep sort) and of several views of up to kBucketMaxTiles together;
     // beyond that of a window of whole views, when a view has at most
-    // kLdsTiles tiles
+    // kLdsTiles tiles, down to a window of one (onesweep / window: 2 views of 1920
+    // x 1080 and 0.5M 345 / 163 us, 8 of them 1145 / 439, 8 of 2M 4182 / 1600, 3 of
+    // 50k 180 / 124, 16 of 20k 359 / 226, 8 of 1280 x 1024 701 / 276; the window's
+    // table makes the workspace of the 8 views 516 MB instead of 195, of the 16
+    // small ones 73 instead of 23)
     p.T = tiles_per_view;
     p.windowed = n_tiles_total > (n_views == 1 ? (int64_t)kLdsTiles : kBucketMaxTiles);
     p.win_views = (int)(kLdsTiles / (tiles_per_view > 0 ? tiles_per_view : 1));

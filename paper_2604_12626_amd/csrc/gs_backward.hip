@@ -105,7 +105,7 @@ enum { kS0 = 0, kSx, kSxx, kSy, kSxy, kSyy, kSums };  // sums of g dx^a dy^b
 // adjoint), consecutive lanes on consecutive adjoints of an entry: an entry's
 // ten meet in one or two cache lines (one entry per lane took twice as long
 // as the rest of the kernel).
-// Bound by the VALU (87 % of its issue; the matrix cores 15 %).  Against a
+// Bound by the VALU (86 % of its issue; the matrix cores 15 %).  Against a
 // 256-thread workgroup per tile whose quadrants walked in step and summed with
 // DPP adds: 16 views of 640 x 480 over 1.4M Gaussians 3577 -> 1640 us, a 1280
 // x 720 view of 1M 341 -> 195 us, a 256 x 256 view of 500k in segments 52.7 ->

@@ -1737,9 +1737,9 @@ __device__ __forceinline__ void merge_tile_runs(uint64_t *bucket, uint64_t *keys
 // Bound by latency: a chain of LDS round trips and barriers per tile, so the
 // registers are bounded to what lets as many workgroups in as the LDS (two
 // fewer of 256 threads and one of 512 cost 30 us of 444 and 160 of 1407 in the
-// frames at sort_lds).  The spread sort against merging levels: 1200 tiles of 300 entries 13.9 -> 11.6
-// us; 18.3M entries in 19200 tiles, all classes, 357 -> 237 us; 23.0M in
-// 16384 tiles 479 -> 275 us.
+// frames at sort_lds).  The spread sort against merging levels: 1200 tiles of
+// 300 entries 13.9 -> 11.6 us; 18.3M entries in 19200 tiles, all classes, 357 ->
+// 187 us; 23.0M in 16384 tiles 479 -> 235 us.
 constexpr int kSortShort = 5, kSortLong = 6;
 
 template <int THREADS, int CAP, int CLASS>
